@@ -3,8 +3,8 @@
 // Pipeline (one stream, one host read-back of sizes):
 //   bbox/validate -> grid of each particle (model, support level) and its
 //   cell key + per-cell counts (atomics) -> scan -> scatter into cell order
-//   -> list of non-empty cells -> finer Morton order inside cells ->
-//   positions gathered in cell order -> per-cell search, count pass -> scan
+//   -> list of non-empty cells and of search items -> finer Morton order inside
+//   cells -> positions gathered in cell order -> search, count pass -> scan
 //   -> fill pass -> per-row sort -> (several support levels: a second cell
 //   pass over each model's finest grid, a model-wide Morton order) ->
 //   grouping of particles by (model, neighbour-count band) for the batched
@@ -146,7 +146,7 @@ struct Grid {
   int nslots;
   int slot0[3];              // slots of model m: [slot0[m], slot0[m + 1])
   double lo[kMaxSlots][3];
-  double inv_edge[kMaxSlots];
+  double edge[kMaxSlots], inv_edge[kMaxSlots];
   double hcap[kMaxSlots];    // every particle of the slot has h <= hcap (0: model absent)
   int dim[kMaxSlots][3];
   int bits[kMaxSlots][3];
@@ -179,6 +179,19 @@ __device__ inline int64_t morton(int cx, int cy, int cz, int bx, int by, int bz)
   return key;
 }
 
+
+// the same for keys below 2^31
+__device__ inline int32_t morton32(int cx, int cy, int cz, int bx, int by, int bz) {
+  uint32_t key = 0;
+  int pos = 0;
+  const int mb = max(bx, max(by, bz));
+  for (int b = 0; b < mb; ++b) {
+    if (b < bx) key |= (((uint32_t)cx >> b) & 1u) << pos++;
+    if (b < by) key |= (((uint32_t)cy >> b) & 1u) << pos++;
+    if (b < bz) key |= (((uint32_t)cz >> b) & 1u) << pos++;
+  }
+  return (int32_t)key;
+}
 
 __global__ void __launch_bounds__(kBlock) k_fill_i32(int32_t *a, int64_t n, int32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -220,14 +233,48 @@ __global__ void __launch_bounds__(kBlock) k_keys(const double *__restrict__ x, c
   slot[i] = mine;
 }
 
-// particles per grid from the scanned cell counts (the cells of a grid are
-// one key range; cell_start[nkeys] = n)
-__global__ void k_slot_count(const int32_t *__restrict__ cell_start, Grid g, int32_t *__restrict__ slot_count) {
-  const int q = threadIdx.x;
-  if (q < g.nslots) {
-    const int64_t e = (q + 1 < g.nslots) ? g.base[q + 1] : g.nkeys;
-    slot_count[q] = cell_start[e] - cell_start[g.base[q]];
+// Search items: the rows of one cell, or of an aligned Morton block of 2, 4 or
+// 8 cells where the grid's cells hold few particles (film cells hold 9; the
+// smallest such block with at least kItemFill particles by the grid's mean over
+// its bounding box), in equal parts of at most `most` rows.  An item's rows are
+// one range of the cell order (a multiple of four but for a unit's last, as the
+// search takes rows in fours), and its candidates are read once for all of
+// them.  items[k] = (first row, rows, grid); their order is left to the run (no
+// result depends on it).  Also the number of particles of each grid.
+constexpr int kItemFill = 20;
+constexpr int kItemBits = 3;
+__global__ void __launch_bounds__(kBlock) k_items(const int32_t *__restrict__ cell_start, Grid g, int most,
+                                                  int4 *__restrict__ items, int32_t *__restrict__ nitems,
+                                                  int32_t *__restrict__ slot_count) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int a = 0, b = 0, s = 0;
+  if (k < g.nkeys) {
+    while (s + 1 < g.nslots && k >= g.base[s + 1]) ++s;
+    const int64_t end = (s + 1 < g.nslots) ? g.base[s + 1] : g.nkeys;
+    const int count = cell_start[end] - cell_start[g.base[s]];
+    if (k == g.base[s]) slot_count[s] = count;
+    const double mean = (double)count / ((double)g.dim[s][0] * g.dim[s][1] * g.dim[s][2]);
+    int sh = 0;
+    while (sh < kItemBits && mean * (double)(1 << sh) < (double)kItemFill && ((int64_t)2 << sh) <= end - g.base[s]) ++sh;
+    if (((k - g.base[s]) & ((1 << sh) - 1)) == 0) {
+      a = cell_start[k];
+      b = cell_start[k + (1 << sh)];
+    }
   }
+  // parts of this unit, and their places (one atomic per wave)
+  const int len = b - a, parts = (len + most - 1) / most;
+  const int lane = threadIdx.x & 63;
+  int inc = parts;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += v;
+  }
+  int at = 0;
+  if (lane == 63 && inc) at = atomicAdd(nitems, inc);
+  at = __builtin_amdgcn_readlane(at, 63) + inc - parts;
+  const int size = ((len + parts - 1) / max(parts, 1) + 3) & ~3;  // <= most
+  for (int q = 0, f = a; f < b; ++q, f += size) items[at + q] = make_int4(f, min(size, b - f), s, 0);
 }
 
 __global__ void __launch_bounds__(kBlock) k_scatter(const int32_t *__restrict__ key, const int32_t *__restrict__ slot,
@@ -367,45 +414,64 @@ __global__ void __launch_bounds__(kBlock) k_gather_pos(const int32_t *__restrict
   int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
   int32_t i = order[s];
-  sp[s] = make_double4(x[i], y[i], z[i], h[i]);
+  sp[s] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
 }
 
 // Eq. (Nbd) predicate, evaluated as written without contraction so that the
-// decision is reproducible across implementations.
+// decision is reproducible across implementations.  The records hold half
+// supports: h_i / 2 + h_j / 2 is 0.5 (h_i + h_j) to the bit (halving is exact).
 __device__ inline bool in_support(double4 a, double4 b) {
 #pragma clang fp contract(off)
   double dx = b.x - a.x;
   double dy = b.y - a.y;
   double dz = b.z - a.z;
   double d2 = (dx * dx + dy * dy) + dz * dz;
-  double r = 0.5 * (a.w + b.w);
+  double r = a.w + b.w;
   return d2 <= r * r;
 }
 
-// Neighbour search, one wave per non-empty cell (waves take the next cell from
-// a queue counter: bulk and film cells differ in cost), its rows in groups of
-// up to 64.  For each target grid (the row
-// model's grids, or all grids for cross-model sets) the cells within
-// R = (max h of the rows + hcap of the grid)/2 of the rows are taken 64 at a
-// time; their particles, numbered through a prefix sum of the cell ranges,
-// are tested 64 at a time (one per lane) against each row, and a ballot gives
-// the row's hits.  MODE 0: count (cnt[i] = |S_i|, group histogram, max row);
-// MODE 1: fill col (each row in candidate order; rows are sorted afterwards).
-// Both passes visit candidates in the same order, so the fill ends exactly at
-// the counted length.  With `stage`, the count pass also writes each row's
-// first sw hits to stage[i * sw ...] (sw, the stage width, 512 or 256 hits
-// by the memory it takes), which saves the fill pass when no row is longer;
-// with `stage` the fill pass writes only the longer rows (and skips the groups
-// of rows without one).  Particles i >= n_rows (ghost particles) appear in the
-// rows of others but their own row holds only i.
+// Neighbour search, one wave per search item (up to kItemRows rows that follow
+// one another in the cell order).
+//  1. The bounding box and the largest support of the item's rows.
+//  2. For each target grid (the row model's grids, or all grids for cross-model
+//     sets) the cells within R = (max h of the rows + hcap of the grid)/2 of
+//     the box are taken 64 at a time and their particles numbered through a
+//     prefix sum of the cell ranges.  Each candidate is tested against the box
+//     with its own support; those that may reach a row go to a ring in LDS.
+//  3. Whenever the ring holds 64 candidates (and at the end), they are tested,
+//     one per lane, against each row, the rows' records in scalar registers,
+//     four rows at a time; a ballot gives a row's hits.
+// MODE 0: count (cnt[i] = |S_i|, group histogram, max row); MODE 1: fill col
+// (rows are sorted afterwards); MODE 2: count, and write each row's first sw
+// hits to stage[i * sw ...] (sw, the stage width, 512 or 256 hits by the memory
+// it takes), which saves the fill pass when no row is longer; with `stage` the
+// fill pass writes only the longer rows.  Hits go out
+// through buffer stores whose range is the row's room: the hardware drops the
+// lanes without a hit (given an offset past any range) and the hits beyond it.
+// Particles i >= n_rows (ghost particles) appear in the rows of others but
+// their own row holds only i.
+//
+// What bounds it: VALU issue and the latency of a wave's serial chain.  A 3D
+// row of the mixed cloud has ~730 candidates in its 27 cells, a row of the
+// uneven jet ~2,700, of which ~100 and ~80 are hits; the box leaves ~450 and
+// ~500.  A test of 64 candidates takes 11 FP64 instructions and 7 more for the
+// output; VALU issue is 60-75% of the launch.  Against the predecessor (one wave
+// per cell, every candidate against every row, ~40 instructions per 64 tests,
+// most of them for the output): mixed cloud 512 -> 216 us, 2.0M jet 3.93 ->
+// 1.68 ms, 25k-particle plate 334 -> 29 us (its few hundred cells left most of
+// the chip idle), 916 particles 53 -> 16 us.  Rows per item at most 8 / 16 / 24
+// / 32: mixed 266 / 231 / 216 / 238 us, jet 2.11 / 1.76 / 1.68 / 1.63 ms.
 constexpr int kSearchBlock = 256;
 constexpr int kSearchWaves = kSearchBlock / 64;
-// occupancy the search kernels are compiled for: five waves per SIMD leave
-// them the registers they use unconstrained (88); asking for six squeezes
-// them into 80 and runs them 15% slower
-constexpr int kSearchWavesPerSimd = 5;
-constexpr int kQueueGrab = 4;           // cells a wave takes from the queue at once
+constexpr int kSearchBlocksPerCu = 8;
+constexpr int kItemRows = 24;
+constexpr int kItemLanes = 32;          // the power of two at or above kItemRows
+constexpr int kRowPad = 4;              // entries of padding after the records and the order (rows are read in fours)
+constexpr int kRing = 128;              // a batch adds at most 64 to at most 63 left over
 constexpr int kStageWidths[2] = {512, 256};  // hits per row the count pass may stage, widest first
+// Items are dealt to the XCDs in chunks: neighbouring items share candidates
+// in one L2, and every XCD gets its share of bulk and film items.
+constexpr int kItemChunk = 128;
 
 // the value of v in lane r (r the same in every lane)
 __device__ inline int64_t readlane64(int64_t v, int r) {
@@ -421,83 +487,164 @@ __device__ inline double uniform_f64(double v) {
   return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
 }
 
+// min / max over the first kItemLanes lanes of the wave, uniform
+__device__ inline double rows_min(double v) {
+#pragma unroll
+  for (int o = kItemLanes / 2; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
+  return uniform_f64(v);
+}
+__device__ inline double rows_max(double v) {
+#pragma unroll
+  for (int o = kItemLanes / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return uniform_f64(v);
+}
+
+// inclusive scans over the wave by lane moves within rows of 16 and row broadcasts
+__device__ inline int wave_scan_add(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+__device__ inline int wave_scan_max(int v) {  // of values >= 0
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+  return v;
+}
+
 template <int MODE>
-__global__ void __launch_bounds__(kSearchBlock) __attribute__((amdgpu_waves_per_eu(kSearchWavesPerSimd))) k_search(const int32_t *__restrict__ order,
+__global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restrict__ order,
                                                          const double4 *__restrict__ sp,
-                                                         const int8_t *__restrict__ model,
                                                          const int32_t *__restrict__ cell_start,
-                                                         const int32_t *__restrict__ cells,
-                                                         const int32_t *__restrict__ ncells,
+                                                         const int4 *__restrict__ items,
+                                                         const int32_t *__restrict__ nitems,
                                                          const int32_t *__restrict__ slot_count,
-                                                         int32_t *__restrict__ queue, int64_t n,
                                                          int64_t n_rows, Grid g, int cross,
                                                          int32_t *__restrict__ cnt, int32_t *__restrict__ hist,
                                                          int32_t *__restrict__ maxrow,
                                                          const int64_t *__restrict__ row_ptr,
                                                          int32_t *__restrict__ col, int32_t *__restrict__ stage,
                                                          int sw) {
-  __shared__ int32_t s_rb[kSearchWaves][64];    // first sorted position of each cell of the batch
-  __shared__ int32_t s_pref[kSearchWaves][65];  // candidates before each cell of the batch
-  __shared__ double4 s_row[kSearchWaves][64];   // positions of the current row group
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int32_t nc = *ncells;
+  __shared__ double2 s_xy[kSearchWaves][kRing], s_zh[kSearchWaves][kRing];  // the ring: positions, half supports,
+  __shared__ int32_t s_id[kSearchWaves][kRing];                             // user indices
+  __shared__ int32_t s_mark[kSearchWaves][64];
+  __shared__ int32_t s_hist[2 * GF_NBAND + 1];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ni = *nitems;
+  if (MODE != 1 && tid <= 2 * GF_NBAND) s_hist[tid] = 0;
   int hist_local = 0;  // lane b < 2*GF_NBAND: rows counted in bin b (MODE 0)
   int max_local = 0;
-  int32_t grab = 0, left = 0;
-  while (true) {
-    if (left == 0) {  // kQueueGrab cells per queue access
-      int32_t next = 0;
-      if (lane == 0) next = atomicAdd(queue, kQueueGrab);
-      grab = __builtin_amdgcn_readfirstlane(next);
-      left = kQueueGrab;
-    }
-    const int32_t ci = grab + (kQueueGrab - left);
-    --left;
-    if (ci >= nc) break;
-    const int32_t c0 = cells[ci];
-    const int32_t c1 = (ci + 1 < nc) ? cells[ci + 1] : (int32_t)n;
-    const int mrow = model[order[c0]];
+  const int nx = gridDim.x % 8 == 0 ? 8 : 1;
+  const int xcd = blockIdx.x % nx, G = gridDim.x / nx * kSearchWaves;
+  constexpr bool STORE = MODE != 0;
+  for (int p = blockIdx.x / nx * kSearchWaves + w;; p += G) {
+    const int chunk = p / kItemChunk;
+    if ((int64_t)chunk * nx * kItemChunk >= ni) break;  // (every later p is past the end too)
+    const int ii = (chunk * nx + xcd) * kItemChunk + p % kItemChunk;
+    if (ii >= ni) continue;
+    const int4 it = items[ii];
+    const int r0 = it.x, nw = it.y;  // rows [r0, r0 + nw), nw <= kItemRows
+    const int mrow = it.z < g.slot0[1] ? 0 : 1;
     const int t0 = cross ? 0 : g.slot0[mrow], t1 = cross ? g.nslots : g.slot0[mrow + 1];
-    for (int32_t rg = c0; rg < c1; rg += 64) {
-      const int nr = min(64, c1 - rg);
-      int32_t myi = -1;
-      bool ghost = false;
-      int64_t myoff = 0;
-      int mylen = 0;  // MODE 1: the row's CSR length (bounds every write)
-      double4 me = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (lane < nr) {
-        myi = order[rg + lane];
-        me = sp[rg + lane];
-        s_row[w][lane] = me;
-        ghost = myi >= n_rows;
-        if (MODE == 1) {
-          myoff = row_ptr[myi];
-          mylen = (int)(row_ptr[myi + 1] - myoff);
-          if (stage && mylen <= sw) mylen = 0;  // staged by the count pass: not written here
-          if (ghost && mylen > 0) col[myoff] = myi;
-        } else if (stage) {
-          myoff = (int64_t)myi * sw;
-          mylen = sw;
-          if (ghost) stage[myoff] = myi;
-        }
+    int32_t myi = -1;
+    bool ghost = false;
+    int64_t myoff = 0;
+    int mylen = 0;  // MODE 1: entries of the row this pass writes
+    double4 me = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (lane < nw) {
+      myi = order[r0 + lane];
+      me = sp[r0 + lane];
+      ghost = myi >= n_rows;
+      if (MODE == 1) {
+        myoff = row_ptr[myi];
+        mylen = (int)(row_ptr[myi + 1] - myoff);
+        if (stage && mylen <= sw) mylen = 0;  // staged by the count pass: not written here
+        if (ghost && mylen > 0) col[myoff] = myi;
+      } else if (MODE == 2) {
+        if (ghost) stage[(int64_t)myi * sw] = myi;
       }
-      if (MODE == 1 && stage && __ballot(mylen > 0) == 0) continue;  // no row of the group to fill
-      const bool act = lane < nr && !ghost;
-      const double bx0 = uniform_f64(wave_min(act ? me.x : INFINITY));
-      const double bx1 = uniform_f64(wave_max(act ? me.x : -INFINITY));
-      const double by0 = uniform_f64(wave_min(act ? me.y : INFINITY));
-      const double by1 = uniform_f64(wave_max(act ? me.y : -INFINITY));
-      const double bz0 = uniform_f64(wave_min(act ? me.z : INFINITY));
-      const double bz1 = uniform_f64(wave_max(act ? me.z : -INFINITY));
-      const double hrow = uniform_f64(wave_max(act ? me.w : 0.0));
-      const uint64_t ghosts = __ballot(ghost);
-      wave_fence();
-      int run = 0;  // lane r < nr: hits of row r so far
+    }
+    const bool act = lane < nw && !ghost && (MODE != 1 || mylen > 0);
+    const unsigned rows = (unsigned)__ballot(act);  // the rows searched
+    int run = 0;  // lane r < nw: hits of row r0 + r so far
+    if (rows) {
+      const double b0[3] = {rows_min(act ? me.x : INFINITY), rows_min(act ? me.y : INFINITY),
+                            rows_min(act ? me.z : INFINITY)};
+      const double b1[3] = {rows_max(act ? me.x : -INFINITY), rows_max(act ? me.y : -INFINITY),
+                            rows_max(act ? me.z : -INFINITY)};
+      const double hrow = rows_max(act ? me.w : 0.0);  // half supports throughout
+      double bc[3], be[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        bc[d] = uniform_f64(0.5 * (b0[d] + b1[d]));
+        be[d] = uniform_f64(fmax(b1[d] - bc[d], bc[d] - b0[d]));
+      }
+      int head = 0, fill = 0;  // the ring: entries [head, head + fill) mod kRing
+      // tests the ring's first min(fill, 64) candidates against the rows
+      auto test = [&]() {
+        wave_fence();
+        const int at = (head + lane) & (kRing - 1);
+        const double2 xy = s_xy[w][at], zh = s_zh[w][at];
+        const int32_t j = s_id[w][at];
+        // (a lane past the fill tests NaN, which no row reaches)
+        const double4 q = make_double4(lane < fill ? xy.x : __builtin_nan(""), xy.y, zh.x, zh.y);
+#pragma unroll 1
+        for (int rq = 0; rq < nw; rq += 4) {
+          // (the records and the order are padded: up to three rows past the item's are read, and masked)
+          double4 pr[4];
+          int32_t ir[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            pr[k] = sp[r0 + rq + k];
+            ir[k] = order[r0 + rq + k];
+          }
+          bool hit[4];
+          int pos[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) hit[k] = in_support(pr[k], q);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            uint64_t m = __ballot(hit[k]);
+            if (!((rows >> (rq + k)) & 1u)) m = 0;
+            const int run_r = __builtin_amdgcn_readlane(run, rq + k);
+            pos[k] = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)run_r));
+            if (lane == rq + k) run = run_r + __popcll(m);
+          }
+          if constexpr (STORE) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              int32_t *out;
+              int lim;
+              if (MODE == 1) {
+                out = col + readlane64(myoff, rq + k);
+                lim = __builtin_amdgcn_readlane(mylen, rq + k);
+              } else {
+                out = stage + (int64_t)ir[k] * sw;
+                lim = sw;
+              }
+              const __amdgpu_buffer_rsrc_t rs =
+                  __builtin_amdgcn_make_buffer_rsrc(out, 0, ((rows >> (rq + k)) & 1u) ? 4 * lim : 0, 0x00020000);
+              __builtin_amdgcn_raw_buffer_store_b32(j, rs, hit[k] ? 4 * pos[k] : -4, 0, 0);
+            }
+          }
+        }
+        const int took = min(fill, 64);
+        head = (head + took) & (kRing - 1);
+        fill -= took;
+        wave_fence();
+      };
+#pragma unroll 1
       for (int ts = t0; ts < t1; ++ts) {
-        if (hrow <= 0.0 || slot_count[ts] == 0) continue;  // no searching row, or an empty grid
+        if (slot_count[ts] == 0) continue;  // an empty grid
         // cells within R of the rows (1e-6 margin against rounding of the cell coordinates)
-        const double R = 0.5 * (hrow + g.hcap[ts]) * (1.0 + 1e-6);
-        const double b0[3] = {bx0, by0, bz0}, b1[3] = {bx1, by1, bz1};
+        const double R = (hrow + 0.5 * g.hcap[ts]) * (1.0 + 1e-6);
         int a0[3], ext[3];
         bool none = false;
 #pragma unroll
@@ -510,106 +657,121 @@ __global__ void __launch_bounds__(kSearchBlock) __attribute__((amdgpu_waves_per_
           ext[d] = __builtin_amdgcn_readfirstlane((int)fmin(f1, top)) - a0[d] + 1;
         }
         if (none) continue;
-        const int64_t nbox = (int64_t)ext[0] * ext[1] * ext[2];
-        for (int64_t kb = 0; kb < nbox; kb += 64) {
+        const unsigned nbox = (unsigned)ext[0] * ext[1] * ext[2];  // <= g.nkeys
+        // (a particle lies in its cell's cube up to the rounding of its cell coordinate, below 1e-9 edges)
+        const double edge = g.edge[ts], Rc = R + 1e-9 * edge;
+#pragma unroll 1
+        for (unsigned kb = 0; kb < nbox; kb += 64) {
           int len = 0, rb = 0;
-          const int64_t kc = kb + lane;
+          const unsigned kc = kb + lane;
           if (kc < nbox) {
-            const int ix = (int)(kc % ext[0]), iy = (int)((kc / ext[0]) % ext[1]), iz = (int)(kc / ((int64_t)ext[0] * ext[1]));
-            const int64_t key = g.base[ts] + morton(a0[0] + ix, a0[1] + iy, a0[2] + iz, g.bits[ts][0], g.bits[ts][1],
-                                                    g.bits[ts][2]);
-            rb = cell_start[key];
-            len = cell_start[key + 1] - rb;
-          }
-          int inc = len;
+            const unsigned q = kc / ext[0], qq = q / ext[1];
+            const int cx = a0[0] + (int)(kc - q * ext[0]), cy = a0[1] + (int)(q - qq * ext[1]), cz = a0[2] + (int)qq;
+            // distance of the cell's cube to the box; the last cell of an axis also holds what lies beyond
+            // it (a grid has at most 10^6 cells per axis)
+            const int cc[3] = {cx, cy, cz};
+            double u2 = 0.0;
 #pragma unroll
-          for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += v;
+            for (int d = 0; d < 3; ++d) {
+              const double lo = fma((double)cc[d], edge, g.lo[ts][d]) - bc[d];  // the cube's faces, from the box's centre
+              const double below = lo - be[d], above = cc[d] == g.dim[ts][d] - 1 ? 0.0 : -(lo + edge) - be[d];
+              const double u = fmax(fmax(below, above), 0.0);
+              u2 = fma(u, u, u2);
+            }
+            if (u2 <= Rc * Rc) {
+              const int32_t key = (int32_t)g.base[ts] + morton32(cx, cy, cz, g.bits[ts][0], g.bits[ts][1], g.bits[ts][2]);
+              rb = cell_start[key];
+              len = cell_start[key + 1] - rb;
+            }
           }
-          s_rb[w][lane] = rb;
-          s_pref[w][lane + 1] = inc;
-          if (lane == 0) s_pref[w][0] = 0;
-          wave_fence();
-          const int C = __shfl(inc, 63, 64);
-          // candidate c's sorted position (c < C): its cell is the largest k
-          // with s_pref[k] <= c
-          auto cand = [&](int c) {
-            int k = 0;
-#pragma unroll
-            for (int step = 32; step > 0; step >>= 1)
-              if (k + step < 64 && s_pref[w][k + step] <= c) k += step;
-            return s_rb[w][k] + (c - s_pref[w][k]);
+          const int pref = wave_scan_add(len) - len;  // candidates before this lane's cell
+          const int C = __builtin_amdgcn_readlane(pref + len, 63);
+          const int delta = rb - pref;                // sorted position of candidate c of this cell: c + delta
+          int carry = 0;                              // 1 + the cell that the last candidate so far falls in
+          // the sorted position of candidate cb + lane: each cell marks its first candidate, and the
+          // largest mark up to a candidate is its cell
+          auto cand = [&](int cb) -> int {
+            s_mark[w][lane] = 0;
+            wave_fence();
+            if (len > 0 && pref >= cb && pref < cb + 64) s_mark[w][pref - cb] = lane + 1;
+            wave_fence();
+            const int mk = max(wave_scan_max(s_mark[w][lane]), carry);
+            wave_fence();
+            carry = __builtin_amdgcn_readlane(mk, 63);
+            return cb + lane + __shfl(delta, mk - 1, 64);
           };
           // the next batch's candidates are requested while this batch is tested
           double4 qn = make_double4(0.0, 0.0, 0.0, 0.0);
-          int32_t qjn = 0;
-          if (lane < C) {
-            const int32_t t = cand(lane);
-            qn = sp[t];
-            if (MODE == 1 || stage) qjn = order[t];
-          }
-          for (int cb = 0; cb < C; cb += 64) {
-            const int c = cb + lane;
-            const bool cv = c < C;
-            const double4 q = qn;
-            const int32_t qj = qjn;
-            if (c + 64 < C) {
-              const int32_t t = cand(c + 64);
+          int32_t jn = 0;
+          if (C > 0) {
+            const int t = cand(0);
+            if (lane < C) {
               qn = sp[t];
-              if (MODE == 1 || stage) qjn = order[t];
-            }
-            // two rows per step: independent chains for the FP64 pipeline
-            for (int r = 0; r < nr; r += 2) {
-              const int r2 = min(r + 1, nr - 1);  // == r when r is the last row
-              const double4 pa = s_row[w][r], pb = s_row[w][r2];
-              const bool ha = cv && !((ghosts >> r) & 1) && in_support(pa, q);
-              const bool hb = r2 != r && cv && !((ghosts >> r2) & 1) && in_support(pb, q);
-              const uint64_t ma = __ballot(ha), mb = __ballot(hb);
-              if (MODE == 1 || stage) {
-                // each row's fill position and output offset, read from its lane (uniform)
-                const int run_a = __builtin_amdgcn_readlane(run, r), run_b = __builtin_amdgcn_readlane(run, r2);
-                const int64_t off_a = readlane64(myoff, r), off_b = readlane64(myoff, r2);
-                const int bef_a = __builtin_amdgcn_mbcnt_hi((uint32_t)(ma >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ma, 0));
-                const int bef_b = __builtin_amdgcn_mbcnt_hi((uint32_t)(mb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mb, 0));
-                const int pos_a = run_a + bef_a, pos_b = run_b + bef_b;
-                int32_t *out = MODE == 1 ? col : stage;
-                if (ha && pos_a < __builtin_amdgcn_readlane(mylen, r)) out[off_a + pos_a] = qj;
-                if (hb && pos_b < __builtin_amdgcn_readlane(mylen, r2)) out[off_b + pos_b] = qj;
-              }
-              if (lane == r) run += __popcll(ma);
-              if (r2 != r && lane == r2) run += __popcll(mb);
+              jn = order[t];
             }
           }
-          wave_fence();
+#pragma unroll 1
+          for (int cb = 0; cb < C; cb += 64) {
+            const double4 q = qn;
+            const int32_t j = jn;
+            const bool cv = cb + lane < C;
+            if (cb + 64 < C) {
+              const int t = cand(cb + 64);
+              if (cb + 64 + lane < C) {
+                qn = sp[t];
+                jn = order[t];
+              }
+            }
+            const double dx = fmax(fabs(q.x - bc[0]) - be[0], 0.0);
+            const double dy = fmax(fabs(q.y - bc[1]) - be[1], 0.0);
+            const double dz = fmax(fabs(q.z - bc[2]) - be[2], 0.0);
+            const double rr = (q.w + hrow) * (1.0 + 1e-6);  // (the differences above are rounded)
+            const bool near = cv && dx * dx + dy * dy + dz * dz <= rr * rr;
+            const uint64_t m = __ballot(near);
+            if (near) {
+              const int at = (head + fill + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))) &
+                             (kRing - 1);
+              s_xy[w][at] = make_double2(q.x, q.y);
+              s_zh[w][at] = make_double2(q.z, q.w);
+              s_id[w][at] = j;
+            }
+            fill += __popcll(m);
+            if (fill >= 64) test();
+          }
         }
       }
-      if (MODE == 0) {
-        int bin = -1;
-        if (lane < nr) {
-          const int cc = ghost ? 1 : run;
-          cnt[myi] = cc;
-          int band = 0;
-          while (band < GF_NBAND - 1 && cc > kBandHi[band]) ++band;
-          bin = model[myi] * GF_NBAND + band;
-          max_local = max(max_local, cc);
-        }
-        // per-wave histogram, all lanes active: lane b counts bin b
+      if (fill > 0) test();
+    }
+    if (MODE != 1) {
+      int bin = -1;
+      if (lane < nw) {
+        const int cc = ghost ? 1 : run;
+        cnt[myi] = cc;
+        int band = 0;
+        while (band < GF_NBAND - 1 && cc > kBandHi[band]) ++band;
+        bin = mrow * GF_NBAND + band;
+        max_local = max(max_local, cc);
+      }
+      // per-wave histogram, all lanes active: lane b counts bin b
 #pragma unroll
-        for (int b = 0; b < 2 * GF_NBAND; ++b) {
-          const int hb = __popcll(__ballot(bin == b));
-          if (lane == b) hist_local += hb;
-        }
+      for (int b = 0; b < 2 * GF_NBAND; ++b) {
+        const int hb = __popcll(__ballot(bin == b));
+        if (lane == b) hist_local += hb;
       }
-      wave_fence();
     }
   }
-  if (MODE == 0) {
-    if (lane < 2 * GF_NBAND && hist_local) atomicAdd(&hist[lane], hist_local);
+  if (MODE != 1) {
+    // one atomic per block and bin (a few addresses for the whole grid)
+    __syncthreads();
+    if (lane < 2 * GF_NBAND && hist_local) atomicAdd(&s_hist[lane], hist_local);
     int cm = max_local;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cm = max(cm, __shfl_xor(cm, o, 64));
-    if (lane == 0 && cm) atomicMax(maxrow, cm);
+    if (lane == 0) atomicMax(&s_hist[2 * GF_NBAND], cm);
+    __syncthreads();
+    if (tid < 2 * GF_NBAND && s_hist[tid]) atomicAdd(&hist[tid], s_hist[tid]);
+    if (tid == 2 * GF_NBAND && s_hist[tid]) atomicMax(maxrow, s_hist[tid]);
   }
 }
 
@@ -1267,6 +1429,7 @@ static Grid finest_grid(const Grid &g) {
         g1.dim[ns][d] = g.dim[s][d];
         g1.bits[ns][d] = g.bits[s][d];
       }
+      g1.edge[ns] = g.edge[s];
       g1.inv_edge[ns] = g.inv_edge[s];
       g1.hcap[ns] = g.hcap[s];
       g1.base[ns] = base;
@@ -1354,6 +1517,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
         edge *= 1.5;
       }
       for (int d = 0; d < 3; ++d) g.lo[ns][d] = empty ? 0.0 : lo[m][d];
+      g.edge[ns] = edge;
       g.inv_edge[ns] = 1.0 / edge;
       g.base[ns] = base;
       base += (int64_t)1 << (g.bits[ns][0] + g.bits[ns][1] + g.bits[ns][2]);
@@ -1367,9 +1531,10 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   // ---- sort particles into cells
   const int64_t K = g.nkeys;
   sz = {sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int32_t) * (K + 1), sizeof(int32_t) * scan_tmp_elems(K + 1),
-        sizeof(double4) * n, sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1), sizeof(int32_t) * 32,
+        sizeof(double4) * (n + kRowPad), sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1),
+        sizeof(int32_t) * 32,
         sizeof(int32_t) * n, sizeof(int32_t) * (n + 1), sizeof(int32_t) * scan_tmp_elems(n + 1),
-        sizeof(int32_t) * n, sizeof(int32_t) * n};
+        sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int4) * n};
   // rows staged by the count pass (sw entries each, the widest that stays
   // under 8 GB); rows found longer are filled by a second search pass
   int sw = 0;
@@ -1382,11 +1547,11 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   int32_t *slot = ar.take<int32_t>(n);
   int32_t *cell_start = ar.take<int32_t>(K + 1);
   int32_t *tmp32 = ar.take<int32_t>(scan_tmp_elems(K + 1));
-  double4 *sp = ar.take<double4>(n);
+  double4 *sp = ar.take<double4>(n + kRowPad);
   int32_t *cnt = ar.take<int32_t>(n);
   int64_t *tmp64 = ar.take<int64_t>(scan_tmp_elems(n + 1));
-  // hist[8], maxrow, -, queue counters of the two search passes [10], [11],
-  // particles per grid [16 .. 16 + kMaxSlots); zeroed before use
+  // hist[8], maxrow, -, search items [10], particles per grid
+  // [16 .. 16 + kMaxSlots); zeroed before use
   int32_t *small = ar.take<int32_t>(32);
   int32_t *slot_count = small + 16;
   int32_t *gflag = ar.take<int32_t>(n);
@@ -1397,6 +1562,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   // pass has finished
   int32_t *cells = ar.take<int32_t>(n);
   int32_t *order1 = ar.take<int32_t>(n);  // model-wide cell order for the grouping (several levels)
+  int4 *items = ar.take<int4>(n);
   int32_t *stage = use_stage ? ar.take<int32_t>((size_t)n * sw) : nullptr;
   int32_t *head = gflag, *cpos = gpos;
   const int32_t *ncells = cpos + n;
@@ -1407,7 +1573,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   nb->cross = cross_model ? 1 : 0;
   auto fail = [&](gf_status s2) { free_nbr(nb); return s2; };
   if (hipMalloc(&nb->row_ptr, sizeof(int64_t) * (n + 1)) != hipSuccess ||
-      hipMalloc(&nb->order, sizeof(int32_t) * n) != hipSuccess ||
+      hipMalloc(&nb->order, sizeof(int32_t) * (n + kRowPad)) != hipSuccess ||
       hipMalloc(&nb->grouped, sizeof(int32_t) * n) != hipSuccess) {
     return fail(set_error(ctx, GF_ENOMEM, "neighbour handle allocation failed"));
   }
@@ -1420,7 +1586,8 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
                      key, slot, cell_start);
   if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "key kernel launch failed"));
   if ((st = scan_i32_to_i32(ctx, cell_start, cell_start, K, tmp32))) return fail(st);
-  hipLaunchKernelGGL(k_slot_count, dim3(1), dim3(64), 0, sm, cell_start, g, slot_count);
+  hipLaunchKernelGGL(k_items, dim3(grid_for(K, kBlock)), dim3(kBlock), 0, sm, cell_start, g, kItemRows, items,
+                     small + 10, slot_count);
   hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, nb->order);
   hipLaunchKernelGGL(k_cell_heads, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, nb->order, key, n, head);
   if ((st = scan_i32_to_i32(ctx, head, cpos, n, tmpg))) return fail(st);
@@ -1433,13 +1600,13 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   hipLaunchKernelGGL(k_gather_pos, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, nb->order, p->x, p->y, p->z, p->h,
                      n, sp);
   }
-  // one wave per non-empty cell from a queue; as many waves as fit at once
-  const dim3 search_grid((unsigned)std::max<int64_t>(
-      1, std::min<int64_t>((n + kSearchWaves - 1) / kSearchWaves, (int64_t)ctx->num_cu * kSearchWavesPerSimd)));
+  // as many blocks as fit at once (fewer on small clouds), a multiple of 8: dealt to the XCDs in turn
+  const dim3 search_grid((unsigned)std::min<int64_t>((n / (2 * kSearchWaves) + 8) / 8 * 8,
+                                                     (int64_t)ctx->num_cu * kSearchBlocksPerCu));
   {
   ProfScope prof_count(ctx, "nbr_count");
-  hipLaunchKernelGGL(k_search<0>, search_grid, dim3(kSearchBlock), 0, sm, nb->order, sp, p->model, cell_start, cells,
-                     ncells, slot_count, small + 10, n, n_rows, g, cross_model ? 1 : 0, cnt, small, small + 8,
+  hipLaunchKernelGGL(use_stage ? k_search<2> : k_search<0>, search_grid, dim3(kSearchBlock), 0, sm, nb->order, sp,
+                     cell_start, items, small + 10, slot_count, n_rows, g, cross_model ? 1 : 0, cnt, small, small + 8,
                      (const int64_t *)nullptr, (int32_t *)nullptr, stage, sw);
   }
   if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "count kernel launch failed"));
@@ -1471,10 +1638,9 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   const bool staged = use_stage;
   if (!staged || nb->max_row > sw) {
     ProfScope prof_fill(ctx, "nbr_fill");
-    hipLaunchKernelGGL(k_search<1>, search_grid, dim3(kSearchBlock), 0, sm, nb->order, sp, p->model, cell_start,
-                       cells, ncells, slot_count, small + 11, n, n_rows, g, cross_model ? 1 : 0, (int32_t *)nullptr,
-                       (int32_t *)nullptr, (int32_t *)nullptr, nb->row_ptr, nb->col, staged ? stage : (int32_t *)nullptr,
-                       sw);
+    hipLaunchKernelGGL(k_search<1>, search_grid, dim3(kSearchBlock), 0, sm, nb->order, sp, cell_start, items,
+                       small + 10, slot_count, n_rows, g, cross_model ? 1 : 0, (int32_t *)nullptr, (int32_t *)nullptr,
+                       (int32_t *)nullptr, nb->row_ptr, nb->col, staged ? stage : (int32_t *)nullptr, sw);
   }
   {
     // staged rows: sorted on their way into the CSR; else sorted in place
