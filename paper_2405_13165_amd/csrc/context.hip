@@ -28,7 +28,11 @@ extern "C" gf_status gf_create(int device, void *stream, gf_ctx **out) {
   ctx->stream = (hipStream_t)stream;
   if (hipSetDevice(device) != hipSuccess) { delete ctx; return GF_EHIP; }
   hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->num_cu = prop.multiProcessorCount;
+  ctx->pool = std::make_shared<BlockPool>();
+  if (hipGetDeviceProperties(&prop, device) == hipSuccess) {
+    ctx->num_cu = prop.multiProcessorCount;
+    ctx->pool->limit = prop.totalGlobalMem / 32;
+  }
   const gf_status st = fixed_scratch_init(ctx);
   if (st != GF_OK) { delete ctx; return st; }
   *out = ctx;
@@ -62,6 +66,13 @@ extern "C" void gf_destroy(gf_ctx *ctx) {
   if (ctx->scratch) {
     (void)hipStreamSynchronize(ctx->stream);
     (void)hipFree(ctx->scratch);
+  }
+  {
+    std::lock_guard<std::mutex> lock(ctx->pool->m);
+    ctx->pool->closed = true;
+    for (auto &b : ctx->pool->blocks) (void)hipFree(b.first);
+    ctx->pool->blocks.clear();
+    ctx->pool->kept = 0;
   }
   if (ctx->host_pinned) (void)hipHostFree(ctx->host_pinned);
   if (ctx->stream_order) (void)hipEventDestroy(ctx->stream_order);
@@ -167,6 +178,69 @@ gf_status ensure_scratch(gf_ctx *ctx, size_t bytes, Arena *arena) {
   arena->base = (char *)ctx->scratch;
   arena->off = 0;
   return GF_OK;
+}
+
+// Blocks come in sizes of eight steps per factor of two, so that the lists of
+// the next step, a little longer or shorter, find the last ones' blocks.
+static size_t block_bytes(size_t bytes) {
+  size_t step = 4096;
+  while (step * 16 < bytes) step *= 2;
+  return (bytes + step - 1) / step * step;
+}
+
+void *nbr_alloc(gf_nbr *nbr, size_t bytes) {
+  const size_t need = block_bytes(bytes ? bytes : 1);
+  BlockPool &p = *nbr->pool;
+  std::pair<void *, size_t> got(nullptr, 0);
+  {
+    std::lock_guard<std::mutex> lock(p.m);
+    size_t best = p.blocks.size();
+    for (size_t k = 0; k < p.blocks.size(); ++k)  // the smallest that fits, at most twice the need
+      if (p.blocks[k].second >= need && p.blocks[k].second <= 2 * need &&
+          (best == p.blocks.size() || p.blocks[k].second < p.blocks[best].second))
+        best = k;
+    if (best < p.blocks.size()) {
+      got = p.blocks[best];
+      p.kept -= got.second;
+      p.blocks.erase(p.blocks.begin() + (long)best);
+    }
+  }
+  if (!got.first) {
+    got.second = need;
+    if (hipMalloc(&got.first, need) != hipSuccess) {
+      // give the kept blocks back and try once more
+      (void)hipGetLastError();
+      {
+        std::lock_guard<std::mutex> lock(p.m);
+        for (auto &b : p.blocks) (void)hipFree(b.first);
+        p.blocks.clear();
+        p.kept = 0;
+      }
+      if (hipMalloc(&got.first, need) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+    }
+  }
+  nbr->blocks.push_back(got);
+  return got.first;
+}
+
+void nbr_release(gf_nbr *nbr) {
+  if (nbr->blocks.empty()) return;
+  BlockPool &p = *nbr->pool;
+  // work that still reads the lists, on any stream, ends before the blocks are handed out again
+  const bool idle = hipDeviceSynchronize() == hipSuccess;
+  std::lock_guard<std::mutex> lock(p.m);
+  for (auto &b : nbr->blocks) {
+    if (idle && !p.closed && p.kept + b.second <= p.limit) {
+      p.blocks.push_back(b);
+      p.kept += b.second;
+    } else {
+      (void)hipFree(b.first);
+    }
+  }
+  nbr->blocks.clear();
 }
 
 gf_status ensure_host(gf_ctx *ctx, size_t bytes) {

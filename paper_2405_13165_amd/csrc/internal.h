@@ -6,10 +6,29 @@
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
+#include <memory>
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/gfdm.h"
+
+// Device memory of freed neighbour handles, kept by the context that built them
+// for its next ones.  A simulation builds and frees its lists every step, and
+// the driver's own calls cost more than the build's kernels on small clouds (a
+// hipMalloc / hipFree pair of 128 MiB takes 55 + 235 us here, and far longer now
+// and then).  At most `limit` bytes are kept (1/32 of the device's memory); the
+// context's end gives everything back.  A handle returns its blocks after the
+// device has finished all work (as hipFree waits), so a block taken from here
+// has no pending use on any stream; the lock covers handles freed from other
+// threads.
+struct BlockPool {
+  std::mutex m;
+  std::vector<std::pair<void *, size_t>> blocks;
+  size_t kept = 0, limit = 0;
+  bool closed = false;  // the context is gone: blocks go straight back to the driver
+};
 
 struct gf_ctx {
   int device = 0;
@@ -35,6 +54,7 @@ struct gf_ctx {
   int ateam[2][4] = {{4, 8, 8, 16}, {4, 8, 8, 16}};
   // LDS staging limit of the tile kernels (gf_set_tile_capacity); 0 = their own
   int tile_cap = 0;
+  std::shared_ptr<BlockPool> pool;
   // optional per-kernel timing with HIP events (gf_profile_enable)
   int profile = 0;
   struct ProfRec {
@@ -62,6 +82,9 @@ enum { GF_NBAND = 4 };
 static const int kBandHi[GF_NBAND] = {24, 48, 128, 1 << 30};
 
 struct gf_nbr {
+  // every device array of the handle: (block, bytes) of `pool`
+  std::vector<std::pair<void *, size_t>> blocks;
+  std::shared_ptr<BlockPool> pool;
   int device = 0;
   int64_t n = 0;
   int64_t nnz = 0;
@@ -69,7 +92,6 @@ struct gf_nbr {
   int cross = 0;
   int64_t *row_ptr = nullptr;  // [n+1]
   int32_t *col = nullptr;      // [nnz]
-  int32_t *order = nullptr;    // [n] particles in cell (Morton) order
   int32_t *grouped = nullptr;  // [n] particles grouped by (model, band), Morton order inside
   int64_t group_start[2 * GF_NBAND + 1] = {0};  // host copy of the group offsets
   int32_t *rev = nullptr;      // [nnz] position of (j,i) for entry (i,j); built lazily
@@ -193,6 +215,10 @@ size_t arena_bytes(const std::vector<size_t> &sizes);
 gf_status fixed_scratch_init(gf_ctx *ctx);
 gf_status ensure_scratch(gf_ctx *ctx, size_t bytes, Arena *arena);
 gf_status ensure_host(gf_ctx *ctx, size_t bytes);
+// a device array owned by the handle (released with it); nullptr if there is no memory
+void *nbr_alloc(gf_nbr *nbr, size_t bytes);
+// releases every array of the handle
+void nbr_release(gf_nbr *nbr);
 
 // validation of a particle struct against a neighbour handle
 gf_status check_particles(gf_ctx *ctx, const gf_particles *p, bool need_kind, bool need_normals);

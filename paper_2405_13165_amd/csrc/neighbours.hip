@@ -102,7 +102,18 @@ __global__ void __launch_bounds__(kBlock) k_bbox(const double *__restrict__ x, c
   }
 }
 
-// one block of kBboxFin threads: thread b takes block partial b (nblk <= kBboxFin)
+// Sizes that the host needs are written by the device straight into the
+// context's pinned host buffer: a copy of a few bytes would be a launch and a
+// gap of its own.  host[k] = a[k] (k < na), host[na] = *last.
+__global__ void k_publish(const int32_t *__restrict__ a, int na, const int64_t *__restrict__ last,
+                          int64_t *__restrict__ host) {
+  const int k = threadIdx.x;
+  if (k < na) host[k] = a[k];
+  if (k == na) host[na] = *last;
+}
+
+// one block of kBboxFin threads: thread b takes block partial b (nblk <= kBboxFin); out and
+// bad_out lie in pinned host memory
 constexpr int kBboxFin = 1024;
 __global__ void __launch_bounds__(kBboxFin) k_bbox_final(const double *__restrict__ part,
                                                          const int *__restrict__ bad_part, int nblk,
@@ -1219,18 +1230,14 @@ int ceil_log2(int v) {
 void free_nbr(gf_nbr *nb) {
   if (!nb) return;
   (void)hipSetDevice(nb->device);
-  if (nb->row_ptr) (void)hipFree(nb->row_ptr);
-  if (nb->col) (void)hipFree(nb->col);
-  if (nb->order) (void)hipFree(nb->order);
-  if (nb->grouped) (void)hipFree(nb->grouped);
-  if (nb->rev) (void)hipFree(nb->rev);
-  if (nb->slot) (void)hipFree(nb->slot);
-  if (nb->tile_u) (void)hipFree(nb->tile_u);
-  if (nb->tile_off) (void)hipFree(nb->tile_off);
-  if (nb->grow_ptr) (void)hipFree(nb->grow_ptr);
-  if (nb->gpos) (void)hipFree(nb->gpos);
-  if (nb->grev) (void)hipFree(nb->grev);
+  nbr_release(nb);
   delete nb;
+}
+
+template <class T>
+bool take(gf_nbr *nb, T *&p, size_t count) {
+  p = static_cast<T *>(nbr_alloc(nb, sizeof(T) * std::max<size_t>(count, 1)));
+  return p != nullptr;
 }
 
 }  // namespace
@@ -1268,10 +1275,7 @@ gf_status ensure_rev(gf_ctx *ctx, gf_nbr *nbr) {
   if (nbr->nnz > (int64_t)0x7fffffff)
     return set_error(ctx, GF_ECAPACITY, "the reverse-edge map holds 32-bit positions; %lld entries exceed it",
                      (long long)nbr->nnz);
-  if (hipMalloc(&nbr->rev, sizeof(int32_t) * std::max<int64_t>(nbr->nnz, 1)) != hipSuccess) {
-    nbr->rev = nullptr;
-    return set_error(ctx, GF_ENOMEM, "reverse-edge map allocation failed");
-  }
+  if (!take(nbr, nbr->rev, nbr->nnz)) return set_error(ctx, GF_ENOMEM, "reverse-edge map allocation failed");
   hipLaunchKernelGGL(k_rev, dim3(grid_for(nbr->n * kRevTeam, kBlock)), dim3(kBlock), 0, ctx->stream, nbr->row_ptr, nbr->col,
                      nbr->n, nbr->rev);
   GF_LAUNCH_CHECK(ctx);
@@ -1315,16 +1319,10 @@ gf_status ensure_grouped_rows(gf_ctx *ctx, gf_nbr *nbr) {
   gf_status st = ensure_rev(ctx, nbr);  // also checks that positions fit 32 bits
   if (st) return st;
   const int64_t n = nbr->n;
-  if (hipMalloc(&nbr->grow_ptr, sizeof(int64_t) * (n + 1)) != hipSuccess ||
-      hipMalloc(&nbr->gpos, sizeof(int32_t) * n) != hipSuccess ||
-      hipMalloc(&nbr->grev, sizeof(int32_t) * std::max<int64_t>(nbr->nnz, 1)) != hipSuccess) {
-    if (nbr->grow_ptr) (void)hipFree(nbr->grow_ptr);
-    if (nbr->gpos) (void)hipFree(nbr->gpos);
-    nbr->grow_ptr = nullptr;
-    nbr->gpos = nullptr;
-    nbr->grev = nullptr;
+  int32_t *grev = nullptr;  // set in the handle last: it says that the maps are there
+  if ((!nbr->grow_ptr && !take(nbr, nbr->grow_ptr, n + 1)) || (!nbr->gpos && !take(nbr, nbr->gpos, n)) ||
+      !take(nbr, grev, nbr->nnz))
     return set_error(ctx, GF_ENOMEM, "grouped row offsets allocation failed");
-  }
   Arena ar;
   if ((st = ensure_scratch(ctx, arena_bytes({sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1)}), &ar)))
     return st;
@@ -1335,8 +1333,9 @@ gf_status ensure_grouped_rows(gf_ctx *ctx, gf_nbr *nbr) {
   GF_LAUNCH_CHECK(ctx);
   if ((st = scan_i32_to_i64(ctx, len, nbr->grow_ptr, n, tmp))) return st;
   hipLaunchKernelGGL(k_grouped_rev, dim3(grid_for(n * kRevTeam, kBlock)), dim3(kBlock), 0, ctx->stream, nbr->grouped,
-                     nbr->row_ptr, nbr->col, nbr->rev, nbr->grow_ptr, nbr->gpos, n, nbr->grev);
+                     nbr->row_ptr, nbr->col, nbr->rev, nbr->grow_ptr, nbr->gpos, n, grev);
   GF_LAUNCH_CHECK(ctx);
+  nbr->grev = grev;
   return GF_OK;
 }
 
@@ -1363,8 +1362,7 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   nb->ntiles = nt;
   if (nt == 0) return GF_OK;
   if (nt >= 0x7fffffff) return set_error(ctx, GF_ECAPACITY, "too many neighbour tiles");
-  if (hipMalloc(&nb->slot, sizeof(uint16_t) * (nb->nnz + kQuadPad)) != hipSuccess ||
-      hipMalloc(&nb->tile_off, sizeof(int64_t) * (nt + 1)) != hipSuccess)
+  if (!take(nb, nb->slot, nb->nnz + kQuadPad) || !take(nb, nb->tile_off, nt + 1))
     return set_error(ctx, GF_ENOMEM, "neighbour tile allocation failed");
   Arena ar;
   std::vector<size_t> sz = {sizeof(int32_t) * nt, sizeof(int64_t) * (nt + 1), sizeof(int64_t) * scan_tmp_elems(nt + 1),
@@ -1389,14 +1387,13 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
     GF_LAUNCH_CHECK(ctx);
     if ((st = scan_i32_to_i64(ctx, cnt, nb->tile_off, nt, tmp64))) return st;
   }
-  if ((st = ensure_host(ctx, 4096))) return st;
-  char *hp = (char *)ctx->host_pinned;
-  GF_HIP(ctx, hipMemcpyAsync(hp, grp_max, sizeof(int32_t) * 16, hipMemcpyDeviceToHost, sm));
-  GF_HIP(ctx, hipMemcpyAsync(hp + 128, nb->tile_off + nt, sizeof(int64_t), hipMemcpyDeviceToHost, sm));
+  int64_t *hp = (int64_t *)ctx->host_pinned;
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, sm, grp_max, 2, nb->tile_off + nt, hp);
+  GF_LAUNCH_CHECK(ctx);
   GF_HIP(ctx, hipStreamSynchronize(sm));
-  for (int q = 0; q < tg.nq; ++q) nb->tile_max[tg.gsel[q]] = ((int32_t *)hp)[q];  // per model
-  const int64_t total = *(int64_t *)(hp + 128);
-  if (hipMalloc(&nb->tile_u, sizeof(int32_t) * std::max<int64_t>(total, 1)) != hipSuccess)
+  for (int q = 0; q < tg.nq; ++q) nb->tile_max[tg.gsel[q]] = (int32_t)hp[q];  // per model
+  const int64_t total = hp[2];
+  if (!take(nb, nb->tile_u, total))
     return set_error(ctx, GF_ENOMEM, "neighbour tile list allocation failed");
   ProfScope prof(ctx, "nbr_tile_compact");
   hipLaunchKernelGGL(k_tile_compact, dim3((unsigned)nt), dim3(kTileThreads), 0, sm, ent_off, nb->tile_off, uniq,
@@ -1458,23 +1455,20 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   // ---- bounding boxes and validation
   const int nblk = (int)std::min<int64_t>(1024, (n + kBlock - 1) / kBlock);
   Arena ar;
-  std::vector<size_t> sz = {sizeof(double) * kBoxVals * nblk, sizeof(int) * nblk, sizeof(double) * kBoxVals, 64};
+  std::vector<size_t> sz = {sizeof(double) * kBoxVals * nblk, sizeof(int) * nblk};
   if ((st = ensure_scratch(ctx, arena_bytes(sz), &ar))) return st;
+  if ((st = ensure_host(ctx, 4096))) return st;
   double *part = ar.take<double>(kBoxVals * nblk);
   int *bad_part = ar.take<int>(nblk);
-  double *box = ar.take<double>(kBoxVals);
-  int *bad = ar.take<int>(16);
+  double *hbox = (double *)ctx->host_pinned;
+  int *hbad = (int *)((char *)ctx->host_pinned + 256);
   hipLaunchKernelGGL(k_bbox, dim3(nblk), dim3(kBlock), 0, sm, p->x, p->y, p->z, p->h, p->model, n, part, bad_part);
   GF_LAUNCH_CHECK(ctx);
   static_assert(kBboxFin >= 1024, "one final thread per bounding-box block");
-  hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kBboxFin), 0, sm, part, bad_part, nblk, box, bad);
+  hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kBboxFin), 0, sm, part, bad_part, nblk, hbox, hbad);
   GF_LAUNCH_CHECK(ctx);
-  if ((st = ensure_host(ctx, 4096))) return st;
-  double *hbox = (double *)ctx->host_pinned;
-  GF_HIP(ctx, hipMemcpyAsync(hbox, box, sizeof(double) * kBoxVals, hipMemcpyDeviceToHost, sm));
-  GF_HIP(ctx, hipMemcpyAsync((char *)ctx->host_pinned + 256, bad, sizeof(int), hipMemcpyDeviceToHost, sm));
   GF_HIP(ctx, hipStreamSynchronize(sm));
-  int nbad = *(int *)((char *)ctx->host_pinned + 256);
+  const int nbad = *hbad;
   if (nbad > 0)
     return set_error(ctx, GF_EINVAL, "%d particles have non-finite coordinates, h <= 0 or a model outside {0,1}", nbad);
   double bx[kBoxVals];
@@ -1534,7 +1528,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
         sizeof(double4) * (n + kRowPad), sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1),
         sizeof(int32_t) * 32,
         sizeof(int32_t) * n, sizeof(int32_t) * (n + 1), sizeof(int32_t) * scan_tmp_elems(n + 1),
-        sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int4) * n};
+        sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int4) * n, sizeof(int32_t) * (n + kRowPad)};
   // rows staged by the count pass (sw entries each, the widest that stays
   // under 8 GB); rows found longer are filled by a second search pass
   int sw = 0;
@@ -1563,20 +1557,19 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   int32_t *cells = ar.take<int32_t>(n);
   int32_t *order1 = ar.take<int32_t>(n);  // model-wide cell order for the grouping (several levels)
   int4 *items = ar.take<int4>(n);
+  int32_t *order = ar.take<int32_t>(n + kRowPad);  // particles in cell order
   int32_t *stage = use_stage ? ar.take<int32_t>((size_t)n * sw) : nullptr;
   int32_t *head = gflag, *cpos = gpos;
   const int32_t *ncells = cpos + n;
 
   gf_nbr *nb = new gf_nbr();
+  nb->pool = ctx->pool;
   nb->device = ctx->device;
   nb->n = n;
   nb->cross = cross_model ? 1 : 0;
   auto fail = [&](gf_status s2) { free_nbr(nb); return s2; };
-  if (hipMalloc(&nb->row_ptr, sizeof(int64_t) * (n + 1)) != hipSuccess ||
-      hipMalloc(&nb->order, sizeof(int32_t) * (n + kRowPad)) != hipSuccess ||
-      hipMalloc(&nb->grouped, sizeof(int32_t) * n) != hipSuccess) {
+  if (!take(nb, nb->row_ptr, n + 1) || !take(nb, nb->grouped, n))
     return fail(set_error(ctx, GF_ENOMEM, "neighbour handle allocation failed"));
-  }
 
   {
   ProfScope prof_cells(ctx, "nbr_cells");
@@ -1588,16 +1581,16 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   if ((st = scan_i32_to_i32(ctx, cell_start, cell_start, K, tmp32))) return fail(st);
   hipLaunchKernelGGL(k_items, dim3(grid_for(K, kBlock)), dim3(kBlock), 0, sm, cell_start, g, kItemRows, items,
                      small + 10, slot_count);
-  hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, nb->order);
-  hipLaunchKernelGGL(k_cell_heads, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, nb->order, key, n, head);
+  hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, order);
+  hipLaunchKernelGGL(k_cell_heads, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, order, key, n, head);
   if ((st = scan_i32_to_i32(ctx, head, cpos, n, tmpg))) return fail(st);
   hipLaunchKernelGGL(k_cell_list, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, head, cpos, n, cells);
   hipLaunchKernelGGL(k_cell_sort_reg, dim3((unsigned)std::min<int64_t>((n + kCellSortWaves - 1) / kCellSortWaves, 4096)),
                      dim3(64 * kCellSortWaves), 0, sm, cells, ncells, n, p->x, p->y, p->z, p->h, p->model, g,
-                     nb->order);
+                     order);
   hipLaunchKernelGGL(k_cell_sort, dim3((unsigned)std::min<int64_t>(n, 2048)), dim3(64), 0, sm, cells, ncells, n,
-                     p->x, p->y, p->z, p->h, p->model, g, nb->order);
-  hipLaunchKernelGGL(k_gather_pos, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, nb->order, p->x, p->y, p->z, p->h,
+                     p->x, p->y, p->z, p->h, p->model, g, order);
+  hipLaunchKernelGGL(k_gather_pos, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, order, p->x, p->y, p->z, p->h,
                      n, sp);
   }
   // as many blocks as fit at once (fewer on small clouds), a multiple of 8: dealt to the XCDs in turn
@@ -1605,20 +1598,18 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
                                                      (int64_t)ctx->num_cu * kSearchBlocksPerCu));
   {
   ProfScope prof_count(ctx, "nbr_count");
-  hipLaunchKernelGGL(use_stage ? k_search<2> : k_search<0>, search_grid, dim3(kSearchBlock), 0, sm, nb->order, sp,
+  hipLaunchKernelGGL(use_stage ? k_search<2> : k_search<0>, search_grid, dim3(kSearchBlock), 0, sm, order, sp,
                      cell_start, items, small + 10, slot_count, n_rows, g, cross_model ? 1 : 0, cnt, small, small + 8,
                      (const int64_t *)nullptr, (int32_t *)nullptr, stage, sw);
   }
   if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "count kernel launch failed"));
   if ((st = scan_i32_to_i64(ctx, cnt, nb->row_ptr, n, tmp64))) return fail(st);
-  int32_t *hsmall = (int32_t *)ctx->host_pinned;
-  if (hipMemcpyAsync(hsmall, small, sizeof(int32_t) * 16, hipMemcpyDeviceToHost, sm) != hipSuccess ||
-      hipMemcpyAsync((char *)ctx->host_pinned + 128, nb->row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, sm) !=
-          hipSuccess ||
-      hipStreamSynchronize(sm) != hipSuccess)
+  const int64_t *hs = (const int64_t *)ctx->host_pinned;  // histogram, longest row, -, entries
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, sm, small, 10, nb->row_ptr + n, (int64_t *)ctx->host_pinned);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(sm) != hipSuccess)
     return fail(set_error(ctx, GF_EHIP, "read-back of neighbour counts failed"));
-  int32_t hist[2 * GF_NBAND];
-  memcpy(hist, hsmall, sizeof(hist));
+  int64_t hist[2 * GF_NBAND];
+  memcpy(hist, hs, sizeof(hist));
   // rows of the tiled bands are grouped together (under band kTileBand) so
   // that tiles stay spatially compact whatever the neighbour count
   for (int m = 0; m < 2; ++m)
@@ -1626,19 +1617,19 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
       hist[m * GF_NBAND + kTileBand] += hist[m * GF_NBAND + band];
       hist[m * GF_NBAND + band] = 0;
     }
-  nb->max_row = hsmall[8];
-  nb->nnz = *(int64_t *)((char *)ctx->host_pinned + 128);
+  nb->max_row = (int32_t)hs[8];
+  nb->nnz = hs[10];
   if (nb->max_row > kMaxRow)
     return fail(set_error(ctx, GF_ECAPACITY, "a particle has %d neighbours; the limit is %d", nb->max_row, kMaxRow));
   if (nb->nnz >= (int64_t)1 << 40) return fail(set_error(ctx, GF_ECAPACITY, "too many neighbour pairs"));
-  if (hipMalloc(&nb->col, sizeof(int32_t) * std::max<int64_t>(nb->nnz, 1)) != hipSuccess)
+  if (!take(nb, nb->col, nb->nnz))
     return fail(set_error(ctx, GF_ENOMEM, "neighbour list allocation (%lld entries) failed", (long long)nb->nnz));
   // staged rows need no fill pass; rows longer than sw (if any) are filled by one that
   // writes only those
   const bool staged = use_stage;
   if (!staged || nb->max_row > sw) {
     ProfScope prof_fill(ctx, "nbr_fill");
-    hipLaunchKernelGGL(k_search<1>, search_grid, dim3(kSearchBlock), 0, sm, nb->order, sp, cell_start, items,
+    hipLaunchKernelGGL(k_search<1>, search_grid, dim3(kSearchBlock), 0, sm, order, sp, cell_start, items,
                        small + 10, slot_count, n_rows, g, cross_model ? 1 : 0, (int32_t *)nullptr, (int32_t *)nullptr,
                        (int32_t *)nullptr, nb->row_ptr, nb->col, staged ? stage : (int32_t *)nullptr, sw);
   }
@@ -1670,7 +1661,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   // of each model's smallest-support grid in Morton order, fine Morton key
   // inside each cell (the same kernels on a grid with one level per model).
   // The arrays of the first cell pass are free once the rows are written.
-  const int32_t *gorder = nb->order;
+  const int32_t *gorder = order;
   if (g.slot0[1] - g.slot0[0] > 1 || g.slot0[2] - g.slot0[1] > 1) {
     ProfScope prof_o(ctx, "nbr_order");
     const Grid g1 = finest_grid(g);

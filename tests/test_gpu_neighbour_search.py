@@ -64,3 +64,23 @@ def test_two_far_clumps():
     d = clumps(24, 3, False)
     d["x"] = np.where(np.arange(len(d["x"])) % 2 == 0, d["x"], d["x"] + 1e5)
     check(d)
+
+
+def test_memory_of_freed_handles():
+    """Handles of different sizes built and freed in turn share the context's kept memory; a handle may outlive its
+    context."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx = g.Context(0)
+    last = None
+    for k, per in enumerate([65, 24, 97, 4, 97]):
+        d = clumps(per, 10 + k, False)
+        nb = g.build_neighbours(ctx, g.Particles.from_dict(ctx, d))
+        rp, col = (t.cpu().numpy() for t in nb.export())
+        rp_o, col_o = oracle.neighbours(d)
+        assert np.array_equal(rp, rp_o) and np.array_equal(col, col_o)
+        if k % 2:
+            nb.close()
+        else:
+            last = nb  # frees the one before it
+    ctx.close()
+    last.close()
