@@ -786,89 +786,87 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
   }
 }
 
-// Sort each row ascending.  One wave per chunk of 64 rows (grid-stride over
-// chunks), the chunk's row offsets one per lane.  A row of up to 128 entries
-// is sorted in registers by a bitonic network of P = the next power of two
-// >= its length: lane l holds positions l and l + 64; exchanges at distance
-// 64 stay in the lane, shorter ones go through cross-lane shuffles.  The
-// next row's entries are loaded while the current one is sorted.  Rows with
-// more than 128 entries (LONG launches only) use a wave-private LDS buffer.
+// Sort each row ascending.  One wave per chunk of rows (grid-stride over
+// chunks), the chunk's row offsets one per lane.  A row is sorted in registers
+// by a bitonic network of P = the next power of two >= its length: lane l holds
+// positions l, l + 64, ...; exchanges at distance 64 and 128 stay in the lane,
+// shorter ones take the partner's value by a lane move and keep the smaller or
+// the larger of the two by a median of three.  Two neighbouring rows of at most
+// 32 entries (film rows) are sorted side by side in the halves of the wave.
+// The next rows' entries are loaded while the current ones are sorted.  Rows
+// with more than 256 entries use a wave-private LDS buffer.
+//
+// What bounds it: VALU issue, 28 stages for a row of 65 to 128 entries.  A
+// stage took a lane move (two and a select at distances 4 and 8, an LDS
+// permute at 16 and 32), a minimum, a maximum and a select; now a lane move and
+// the median.  Chunks shrink on small clouds, whose few long chunks left most of
+// the chip idle.  Mixed cloud 225 -> 120 us, 2.0M jet 1.23 -> 0.65 ms, 25k-particle
+// plate 99 -> 12 us, 916 particles 49 -> 4 us.
 constexpr int kSortBlock = 256;
 constexpr int kSortWaves = kSortBlock / 64;
+constexpr int kSortChunk = 64;   // rows of a chunk, at most
+constexpr int kNoEntry = 0x7fffffff;
 
-// v of lane `lane ^ j` (j a power of two up to 32, a constant once the
-// networks are unrolled), without the LDS crossbar where a lane move does it:
-// j = 1, 2 by a DPP quad permutation, j = 4, 8 by the two DPP row shifts and a
-// select (a lane with bit j clear reads lane + j, one with it set lane - j,
-// both in its row of 16), j = 16 by a swizzle within 32 lanes (bitmask mode,
-// xor 16), j = 32 by a permute.  Every lane of the wave is active here.
-__device__ __forceinline__ int32_t xor_lane(int32_t v, int j, int lane) {
+// the median of three signed integers (one instruction)
+__device__ __forceinline__ int32_t med3(int32_t a, int32_t b, int32_t c) { return max(min(a, b), min(max(a, b), c)); }
+
+// One exchange at distance j (a power of two up to 32, a constant once the
+// networks are unrolled) between lanes: the smaller of v and lane ^ j's value
+// where bound is -1, the larger where it is kNoEntry (entries are >= 0).  The
+// partner comes by a DPP quad permutation (1, 2), a half-row mirror and a quad
+// mirror (4: 7 xor 3), a row rotation by half a row (8) or the swaps of rows
+// and half waves (16, 32), which give both values of the pair at once.  Every
+// lane of the wave is active here.
+__device__ __forceinline__ int32_t exchange(int32_t v, int j, int32_t bound) {
   switch (j) {
-    case 1: return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false);  // quad_perm [1, 0, 3, 2]
-    case 2: return __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false);  // quad_perm [2, 3, 0, 1]
+    case 1: return med3(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true), bound);  // quad_perm [1, 0, 3, 2]
+    case 2: return med3(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true), bound);  // quad_perm [2, 3, 0, 1]
     case 4: {
-      const int32_t up = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0xF, false);  // row_shl:4
-      const int32_t dn = __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-      return (lane & 4) ? dn : up;
+      const int32_t m = __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);             // row_half_mirror
+      return med3(v, __builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, true), bound);         // quad_perm [3, 2, 1, 0]
     }
-    case 8: {
-      const int32_t up = __builtin_amdgcn_update_dpp(v, v, 0x108, 0xF, 0xF, false);  // row_shl:8
-      const int32_t dn = __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-      return (lane & 8) ? dn : up;
+    case 8: return med3(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true), bound);  // row_ror:8
+    case 16: {
+      const auto s = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+      return med3((int32_t)s[0], (int32_t)s[1], bound);
     }
-    case 16: return __builtin_amdgcn_ds_swizzle(v, (16 << 10) | 0x1F);
-    default: return __shfl_xor(v, j, 64);
+    default: {
+      const auto s = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+      return med3((int32_t)s[0], (int32_t)s[1], bound);
+    }
   }
 }
 
-__device__ inline int32_t bitonic_pick(int32_t v, int32_t partner, int t, int j, int k) {
-  const bool up = (t & k) == 0;     // direction of this k-sequence
-  const bool lower = (t & j) == 0;  // t is the smaller position of its pair
-  return (lower == up) ? min(v, partner) : max(v, partner);
-}
-
-// the bitonic network for P (power of two, <= 128) elements, unrolled
-template <int P>
-__device__ inline void sort_net(int32_t &v0, int32_t &v1, int lane) {
+// The bitonic network for P (power of two) elements, position lane + 64 r in
+// v[r] (P <= 64: v[0] alone; P <= 32: independently in every group of P lanes).
+// low[b]: -1 in the lanes whose bit b is clear, else kNoEntry; the bounds of a
+// descending sequence differ from an ascending one's in the top bit.
+template <int P, int NV>
+__device__ inline void sort_net(int32_t (&v)[NV], int lane, const int32_t (&low)[6]) {
+  constexpr int R = P <= 64 ? 1 : P / 64;
+  static_assert(R <= NV, "the network needs a register per 64 positions");
 #pragma unroll
   for (int k = 2; k <= P; k <<= 1) {
+    const int32_t flip = (k < 64 && k < P && (lane & k)) ? (int32_t)0x80000000 : 0;
 #pragma unroll
     for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j == 64) {
-        const int32_t lo = min(v0, v1), hi = max(v0, v1);
-        v0 = lo;
-        v1 = hi;
+      if (j >= 64) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int o = r ^ (j / 64);
+          if (o < r) continue;
+          const bool up = ((64 * r) & k) == 0;
+          const int32_t a = min(v[r], v[o]), b = max(v[r], v[o]);
+          v[r] = up ? a : b;
+          v[o] = up ? b : a;
+        }
       } else {
-        v0 = bitonic_pick(v0, xor_lane(v0, j, lane), lane, j, k);
-        if (P > 64) v1 = bitonic_pick(v1, xor_lane(v1, j, lane), lane + 64, j, k);
-      }
-    }
-  }
-}
-
-// the bitonic network for 256 elements, four per lane (position lane + 64 r
-// in v[r]): distances 128 and 64 compare registers of one lane, shorter ones
-// exchange through the wave
-__device__ inline void sort_net256(int32_t v[4], int lane) {
-  auto cx = [](int32_t &a, int32_t &b, int t, int k) {  // a at position t, b at t + distance
-    const bool up = (t & k) == 0;
-    const int32_t lo = min(a, b), hi = max(a, b);
-    a = up ? lo : hi;
-    b = up ? hi : lo;
-  };
+        const int bit = j == 1 ? 0 : j == 2 ? 1 : j == 4 ? 2 : j == 8 ? 3 : j == 16 ? 4 : 5;
 #pragma unroll
-  for (int k = 2; k <= 256; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j == 128) {
-        cx(v[0], v[2], lane, k);
-        cx(v[1], v[3], lane + 64, k);
-      } else if (j == 64) {
-        cx(v[0], v[1], lane, k);
-        cx(v[2], v[3], lane + 128, k);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = bitonic_pick(v[r], xor_lane(v[r], j, lane), lane + 64 * r, j, k);
+        for (int r = 0; r < R; ++r) {
+          const bool down = k >= 64 && k < P && ((64 * r) & k) != 0;
+          v[r] = exchange(v[r], j, low[bit] ^ (down ? (int32_t)0x80000000 : flip));
+        }
       }
     }
   }
@@ -877,15 +875,20 @@ __device__ inline void sort_net256(int32_t v[4], int lane) {
 // STAGED: a row of at most sw entries is read from stage[i * sw ...]
 // (the count pass's copy) and written, sorted, to its CSR place; a longer row
 // (filled by the fill pass), or every row without STAGED, is sorted in place.
+// LONG: rows of more than 128 entries exist.
 template <bool LONG, bool STAGED>
-__global__ void __launch_bounds__(kSortBlock) k_row_sort(const int64_t *__restrict__ row_ptr, int32_t *__restrict__ col,
-                                                         const int32_t *__restrict__ stage, int sw, int64_t n) {
-  extern __shared__ int32_t sort_buf[];  // LONG: kSortWaves x kMaxRow
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t nchunks = (n + 63) / 64;
+__global__ void __launch_bounds__(kSortBlock) k_row_sort(const int64_t *__restrict__ row_ptr, int32_t *col,
+                                                         const int32_t *__restrict__ stage, int sw, int64_t n,
+                                                         int chunk) {
+  extern __shared__ int32_t sort_buf[];  // rows of more than 256 entries: kSortWaves x kMaxRow
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int32_t low[6];
+#pragma unroll
+  for (int b = 0; b < 6; ++b) low[b] = (lane >> b) & 1 ? kNoEntry : -1;
+  const int64_t nchunks = (n + chunk - 1) / chunk;
   for (int64_t ch = (int64_t)blockIdx.x * kSortWaves + w; ch < nchunks; ch += (int64_t)gridDim.x * kSortWaves) {
-    const int64_t i0 = ch * 64;
-    const int nr = (int)min((int64_t)64, n - i0);
+    const int64_t i0 = ch * chunk;
+    const int nr = (int)min((int64_t)chunk, n - i0);
     int64_t rb = 0;
     int rl = 0;
     if (lane < nr) {
@@ -899,44 +902,57 @@ __global__ void __launch_bounds__(kSortBlock) k_row_sort(const int64_t *__restri
     // rows of up to kRegRow entries are held in registers (NV per lane)
     constexpr int NV = LONG ? 4 : 2;
     constexpr int kRegRow = 64 * NV;
-    auto fetch = [&](int r, int32_t a[NV]) {
-      const int32_t *sr = src(r);
-      const int len = __builtin_amdgcn_readlane(rl, r);
+    // whether rows r and r + 1 are sorted side by side
+    auto paired = [&](int r) {
+      return r + 1 < nr && __builtin_amdgcn_readlane(rl, r) <= 32 && __builtin_amdgcn_readlane(rl, r + 1) <= 32;
+    };
+    auto fetch = [&](int r, int32_t (&a)[NV]) {
 #pragma unroll
-      for (int q = 0; q < NV; ++q) a[q] = (len <= kRegRow && lane + 64 * q < len) ? sr[lane + 64 * q] : 0x7fffffff;
+      for (int q = 0; q < NV; ++q) a[q] = kNoEntry;
+      if (r >= nr) return;
+      const int len = __builtin_amdgcn_readlane(rl, r);
+      const int32_t *sr = src(r);
+      if (paired(r)) {
+        const int len1 = __builtin_amdgcn_readlane(rl, r + 1);
+        const int32_t *s1 = src(r + 1);
+        const int32_t *mine = lane < 32 ? sr + lane : s1 + (lane - 32);
+        if ((lane & 31) < (lane < 32 ? len : len1)) a[0] = *mine;
+      } else if (len <= kRegRow) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+          if (lane + 64 * q < len) a[q] = sr[lane + 64 * q];
+      }
     };
     int32_t v[NV];
     fetch(0, v);
-    for (int r = 0; r < nr; ++r) {
+    for (int r = 0; r < nr;) {
       const int64_t b = readlane64(rb, r);
       const int len = __builtin_amdgcn_readlane(rl, r);
+      const bool two = paired(r);
       int32_t nx[NV];
+      fetch(r + (two ? 2 : 1), nx);
+      if (two) {
+        const int64_t b1 = readlane64(rb, r + 1);
+        const int len1 = __builtin_amdgcn_readlane(rl, r + 1);
+        if (max(len, len1) <= 8) sort_net<8, NV>(v, lane, low);
+        else if (max(len, len1) <= 16) sort_net<16, NV>(v, lane, low);
+        else sort_net<32, NV>(v, lane, low);
+        if ((lane & 31) < (lane < 32 ? len : len1)) col[(lane < 32 ? b : b1) + (lane & 31)] = v[0];
+      } else if (len <= kRegRow) {
+        if (len <= 16) sort_net<16, NV>(v, lane, low);
+        else if (len <= 32) sort_net<32, NV>(v, lane, low);
+        else if (len <= 64) sort_net<64, NV>(v, lane, low);
+        else if (len <= 128) sort_net<128, NV>(v, lane, low);
+        else if constexpr (LONG) sort_net<256, NV>(v, lane, low);
 #pragma unroll
-      for (int q = 0; q < NV; ++q) nx[q] = 0x7fffffff;
-      if (r + 1 < nr) fetch(r + 1, nx);
-      if (STAGED && len == 1) {
-        if (lane == 0) col[b] = v[0];
-      } else if (len > 1 && len <= 128) {
-        if (len <= 8) sort_net<8>(v[0], v[1], lane);
-        else if (len <= 16) sort_net<16>(v[0], v[1], lane);
-        else if (len <= 32) sort_net<32>(v[0], v[1], lane);
-        else if (len <= 64) sort_net<64>(v[0], v[1], lane);
-        else sort_net<128>(v[0], v[1], lane);
-        if (lane < len) col[b + lane] = v[0];
-        if (lane + 64 < len) col[b + lane + 64] = v[1];
-      } else if (LONG && len > 128 && len <= kRegRow) {
-        if constexpr (LONG) {
-          sort_net256(v, lane);
-#pragma unroll
-          for (int q = 0; q < NV; ++q)
-            if (lane + 64 * q < len) col[b + lane + 64 * q] = v[q];
-        }
-      } else if (LONG && len > kRegRow) {
+        for (int q = 0; q < NV; ++q)
+          if (lane + 64 * q < len) col[b + lane + 64 * q] = v[q];
+      } else if constexpr (LONG) {
         int32_t *bw = sort_buf + w * kMaxRow;
         const int32_t *sr = src(r);
         int P = 1;
         while (P < len) P <<= 1;
-        for (int t = lane; t < P; t += 64) bw[t] = (t < len) ? sr[t] : 0x7fffffff;
+        for (int t = lane; t < P; t += 64) bw[t] = (t < len) ? sr[t] : kNoEntry;
         wave_fence();
         for (int k = 2; k <= P; k <<= 1) {
           for (int j = k >> 1; j > 0; j >>= 1) {
@@ -955,6 +971,7 @@ __global__ void __launch_bounds__(kSortBlock) k_row_sort(const int64_t *__restri
       }
 #pragma unroll
       for (int q = 0; q < NV; ++q) v[q] = nx[q];
+      r += two ? 2 : 1;
     }
   }
 }
@@ -1636,21 +1653,24 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   {
     // staged rows: sorted on their way into the CSR; else sorted in place
     ProfScope prof_sort(ctx, "nbr_row_sort");
-    const int64_t nchunks = (n + 63) / 64;
+    // chunks of at most kSortChunk rows, fewer where the cloud would not give every SIMD eight waves
+    int chunk = kSortChunk;
+    while (chunk > 2 && n / chunk < (int64_t)ctx->num_cu * 32) chunk /= 2;
+    const int64_t nchunks = (n + chunk - 1) / chunk;
     const dim3 sgrid((unsigned)std::max<int64_t>(1, std::min<int64_t>((nchunks + kSortWaves - 1) / kSortWaves, 4096)));
-    const size_t lds = nb->max_row > 128 ? sizeof(int32_t) * kSortWaves * kMaxRow : 0;
+    const size_t lds = nb->max_row > 256 ? sizeof(int32_t) * kSortWaves * kMaxRow : 0;
     if (staged && nb->max_row > 128)
-      hipLaunchKernelGGL((k_row_sort<true, true>), sgrid, dim3(kSortBlock), lds, sm, nb->row_ptr, nb->col, stage, sw,
-                         n);
+      hipLaunchKernelGGL((k_row_sort<true, true>), sgrid, dim3(kSortBlock), lds, sm, nb->row_ptr, nb->col, stage, sw, n,
+                         chunk);
     else if (staged)
-      hipLaunchKernelGGL((k_row_sort<false, true>), sgrid, dim3(kSortBlock), 0, sm, nb->row_ptr, nb->col, stage, sw,
-                         n);
+      hipLaunchKernelGGL((k_row_sort<false, true>), sgrid, dim3(kSortBlock), 0, sm, nb->row_ptr, nb->col, stage, sw, n,
+                         chunk);
     else if (nb->max_row > 128)
       hipLaunchKernelGGL((k_row_sort<true, false>), sgrid, dim3(kSortBlock), lds, sm, nb->row_ptr, nb->col,
-                         (const int32_t *)nullptr, 0, n);
+                         (const int32_t *)nullptr, 0, n, chunk);
     else
       hipLaunchKernelGGL((k_row_sort<false, false>), sgrid, dim3(kSortBlock), 0, sm, nb->row_ptr, nb->col,
-                         (const int32_t *)nullptr, 0, n);
+                         (const int32_t *)nullptr, 0, n, chunk);
   }
   if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "fill/sort kernel launch failed"));
 
