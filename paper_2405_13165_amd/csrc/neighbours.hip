@@ -1021,35 +1021,23 @@ __device__ inline int tile_group(const TileGroups &tg, int64_t t) {
   return q;
 }
 
-// number of neighbour entries of each tile
-__global__ void __launch_bounds__(kBlock) k_tile_entries(TileGroups tg, const int64_t *__restrict__ row_ptr,
-                                                         const int32_t *__restrict__ grouped,
-                                                         int32_t *__restrict__ ent) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= tg.tile_start[tg.nq]) return;
-  const int q = tile_group(tg, t);
-  const int64_t r0 = (t - tg.tile_start[q]) * kTileRows;
-  const int64_t r1 = min(r0 + kTileRows, tg.nrows[q]);
-  int64_t e = 0;
-  for (int64_t r = r0; r < r1; ++r) {
-    const int32_t i = grouped[tg.row_start[q] + r];
-    e += row_ptr[i + 1] - row_ptr[i];
-  }
-  ent[t] = (int32_t)e;
-}
-
 // One block per tile.  The tile's distinct indices go into an LDS hash set
-// (open addressing, linear probing); a new key also takes the next place in
-// ulist (one counter update per wave) and records where it sits in the
-// table.  The distinct indices are ranked by counting (rank = number of
-// smaller distinct indices), each rank is kept beside its key, the sorted list
-// is written to uniq[ent_off[t] ...], and each entry's slot is the rank of its
-// index, read at the table position its insertion found; cnt[t] = number of
-// distinct indices.  Each wave takes whole rows (w, w + 8, ...), a lane at
-// most two entries of each (rows hold at most kTileBandRow = 128 entries):
-// its column indices are all requested at once and stay in registers, with
-// their table positions, until the slots are written.  The result does not
-// depend on the order of the insertions.
+// (open addressing, linear probing); the lane that inserts a key also takes a
+// place for it in ulist (one counter update per wave).  The list is sorted in
+// groups of 64 in registers, a key's rank is its place in its group plus the
+// number of smaller keys of every other group (binary searches side by side),
+// the sorted list is written to uniq[kTileEntries t ...], and each entry's slot is
+// the rank kept beside its key, read at the table position its insertion found;
+// cnt[t] = number of distinct indices.  Each wave takes whole rows (w, w + 8,
+// ...), a lane at most two entries of each (rows hold at most kTileBandRow = 128
+// entries): its column indices are all requested at once, and all tried in the
+// table at once, and stay in registers, with their table positions, until the
+// slots are written.  The result does not depend on the order of the insertions.
+//
+// What bounds it: VALU issue and LDS latency.  A 3D tile of the mixed cloud
+// has 460 distinct indices of 3,300; ranking each against all the others took
+// two thirds of the kernel's instructions.  Mixed cloud 265 -> 193 us, 2.0M jet
+// 835 -> 744 us (and the launch that counted each tile's entries, 20 and 28 us).
 constexpr int kHashBits = 12;
 constexpr int kHashSize = 1 << kHashBits;  // >= kTileEntries >= distinct keys: every probe ends
 static_assert(kHashSize >= kTileEntries, "the hash set must hold every entry of a tile");
@@ -1059,130 +1047,127 @@ __device__ inline int hash_slot(int32_t j) { return (int)(((uint32_t)j * 2654435
 __global__ void __launch_bounds__(kTileThreads) k_tile_unique(TileGroups tg, const int64_t *__restrict__ row_ptr,
                                                               const int32_t *__restrict__ col,
                                                               const int32_t *__restrict__ grouped,
-                                                              const int64_t *__restrict__ ent_off,
                                                               uint16_t *__restrict__ slot,
                                                               int32_t *__restrict__ uniq, int32_t *__restrict__ cnt,
                                                               int32_t *__restrict__ grp_max) {
   constexpr int NW = kTileThreads / 64;
   __shared__ int32_t hkey[kHashSize];
-  __shared__ uint16_t hrank[kHashSize];
-  __shared__ __attribute__((aligned(16))) int32_t ulist[kTileEntries];  // distinct indices, then sorted
-  __shared__ uint16_t upos[kTileEntries];                                // table position of ulist[s]
-  __shared__ int64_t rbase[kTileRows];
-  __shared__ int32_t rlen[kTileRows];
-  __shared__ int32_t ucount;
+  __shared__ __attribute__((aligned(4))) uint16_t hrank[kHashSize];
+  __shared__ int32_t ulist[kTileEntries];  // distinct indices, sorted in groups of 64
+  // the list's length lies where the ranks go later: 40,960 bytes let four blocks share a CU
+  int32_t &ucount = *reinterpret_cast<int32_t *>(hrank);
   const int64_t t = blockIdx.x;
   const int q = tile_group(tg, t);
   const int64_t r0 = (t - tg.tile_start[q]) * kTileRows;
   const int R = (int)min((int64_t)kTileRows, tg.nrows[q] - r0);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  if (tid < R) {
-    const int32_t i = grouped[tg.row_start[q] + r0 + tid];
-    rbase[tid] = row_ptr[i];
-    rlen[tid] = (int)(row_ptr[i + 1] - row_ptr[i]);  // <= kTileBandRow: tiled rows
-  }
-  for (int h = tid; h < kHashSize; h += kTileThreads) hkey[h] = -1;
-  if (tid == 0) ucount = 0;
-  __syncthreads();
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   // 1. distinct indices; entry c of a lane: row wave + NW (c / 2), entry lane + 64 (c % 2)
   static_assert(kTileRows == 4 * NW && kTileBandRow == 128, "four rows per wave, two entries per lane and row");
   constexpr int kC = 8;
+  int64_t base[kC / 2];
   int32_t jj[kC];
   int hh[kC];
 #pragma unroll
-  for (int c = 0; c < kC; ++c) {
-    const int r = wave + NW * (c >> 1), e = lane + 64 * (c & 1);
-    jj[c] = (r < R && e < rlen[r]) ? col[rbase[r] + e] : -1;
+  for (int c = 0; c < kC; c += 2) {
+    const int r = wave + NW * (c >> 1);
+    base[c / 2] = 0;
+    int len = 0;
+    if (r < R) {
+      const int32_t i = grouped[tg.row_start[q] + r0 + r];
+      base[c / 2] = row_ptr[i];
+      len = (int)(row_ptr[i + 1] - base[c / 2]);  // <= kTileBandRow: tiled rows
+    }
+    jj[c] = lane < len ? col[base[c / 2] + lane] : -1;
+    jj[c + 1] = lane + 64 < len ? col[base[c / 2] + lane + 64] : -1;
   }
+  {
+    const int4 none = make_int4(-1, -1, -1, -1);
+    int4 *h4 = reinterpret_cast<int4 *>(hkey);
+    for (int h = tid; h < kHashSize / 4; h += kTileThreads) h4[h] = none;
+  }
+  if (tid == 0) ucount = 0;
+  __syncthreads();
+  int32_t prev[kC];
 #pragma unroll
   for (int c = 0; c < kC; ++c) {
-    {
-      const int32_t j = jj[c];
-      bool fresh = false;
-      int h = 0;
-      if (j >= 0) {
-        h = hash_slot(j);
-        while (true) {
-          const int32_t prev = atomicCAS(&hkey[h], -1, j);
-          if (prev == -1) {
-            fresh = true;
-            break;
-          }
-          if (prev == j) break;
-          h = (h + 1) & (kHashSize - 1);
-        }
-      }
-      hh[c] = h;
-      const uint64_t m = __ballot(fresh);
-      int ub = 0;
-      if (lane == 0 && m) ub = atomicAdd(&ucount, __popcll(m));
-      ub = __shfl(ub, 0, 64);
-      if (fresh) {
-        const int s = ub + __popcll(m & ((1ull << lane) - 1));
-        ulist[s] = j;
-        upos[s] = (uint16_t)h;
-      }
+    hh[c] = hash_slot(jj[c]);
+    prev[c] = jj[c] >= 0 ? atomicCAS(&hkey[hh[c]], -1, jj[c]) : jj[c];
+  }
+  int fresh = 0;  // bit c: this lane inserted entry c's key
+#pragma unroll
+  for (int c = 0; c < kC; ++c) {
+    while (prev[c] != -1 && prev[c] != jj[c]) {
+      hh[c] = (hh[c] + 1) & (kHashSize - 1);
+      prev[c] = atomicCAS(&hkey[hh[c]], -1, jj[c]);
+    }
+    if (prev[c] == -1 && jj[c] >= 0) fresh |= 1 << c;
+  }
+  {
+    const int mine = __popc(fresh), inc = wave_scan_add(mine);
+    int ub = 0;
+    if (lane == 63 && inc) ub = atomicAdd(&ucount, inc);
+    int s = __builtin_amdgcn_readlane(ub, 63) + inc - mine;
+#pragma unroll
+    for (int c = 0; c < kC; ++c)
+      if ((fresh >> c) & 1) ulist[s++] = jj[c];
+  }
+  __syncthreads();
+  const int U = ucount, NG = (U + 63) / 64;
+  // 2. groups of 64 sorted in place (the last one padded with kNoEntry)
+  int32_t low[6];
+#pragma unroll
+  for (int b = 0; b < 6; ++b) low[b] = (lane >> b) & 1 ? kNoEntry : -1;
+  for (int gi = wave; gi < NG; gi += NW) {
+    int32_t v[1] = {64 * gi + lane < U ? ulist[64 * gi + lane] : kNoEntry};
+    sort_net<64, 1>(v, lane, low);
+    ulist[64 * gi + lane] = v[0];
+  }
+  __syncthreads();
+  // 3. ranks: to the sorted list, and beside the keys
+  for (int gi = wave; gi < NG; gi += NW) {
+    const int32_t v = ulist[64 * gi + lane];
+    int rank = lane;
+    for (int o = 0; o < NG; o += 4) {  // four groups' searches side by side
+      int lo[4] = {0, 0, 0, 0};
+      const int32_t *l[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) l[k] = ulist + 64 * min(o + k, NG - 1);
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (l[k][lo[k] + step - 1] < v) lo[k] += step;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (o + k < NG && o + k != gi) rank += lo[k] + (l[k][lo[k]] < v ? 1 : 0);
+    }
+    if (v != kNoEntry) {
+      uniq[kTileEntries * t + rank] = v;
+      int h = hash_slot(v);
+      while (hkey[h] != v) h = (h + 1) & (kHashSize - 1);
+      hrank[h] = (uint16_t)rank;
     }
   }
-  __syncthreads();
-  const int U = ucount;
-  // 2. rank of each distinct index = number of smaller distinct indices; the
-  // list is read four at a time (padded to a multiple of four), every lane
-  // of a wave reading the same address (an LDS broadcast).  The ranks go
-  // beside the keys, and (after a barrier) the list is sorted in place.
-  const int U4 = (U + 3) & ~3;
-  for (int s = U + tid; s < U4; s += kTileThreads) ulist[s] = 0x7fffffff;
-  __syncthreads();
-  constexpr int kPer = kTileEntries / kTileThreads;
-  int32_t vv[kPer];
-  int rr[kPer];
-#pragma unroll
-  for (int c = 0; c < kPer; ++c) {
-    const int s = tid + c * kTileThreads;
-    rr[c] = -1;
-    vv[c] = 0;
-    if (s < U) {
-      const int32_t v = ulist[s];
-      int r = 0;
-      const int4 *l4 = reinterpret_cast<const int4 *>(ulist);
-      for (int c4 = 0; c4 < U4 / 4; ++c4) {
-        const int4 w4 = l4[c4];
-        r += (w4.x < v) + (w4.y < v) + (w4.z < v) + (w4.w < v);
-      }
-      vv[c] = v;
-      rr[c] = r;
-      hrank[upos[s]] = (uint16_t)r;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < kPer; ++c)
-    if (rr[c] >= 0) ulist[rr[c]] = vv[c];
-  __syncthreads();
-  // 3. the sorted distinct indices
-  const int64_t ubase = ent_off[t];
-  for (int s = tid; s < U; s += kTileThreads) uniq[ubase + s] = ulist[s];
   if (tid == 0) {
     cnt[t] = U;
     atomicMax(&grp_max[q], U);
   }
+  __syncthreads();
   // 4. slots: the rank kept beside each entry's index
 #pragma unroll
   for (int c = 0; c < kC; ++c)
-    if (jj[c] >= 0) {
-      const int r = wave + NW * (c >> 1), e = lane + 64 * (c & 1);
-      slot[rbase[r] + e] = hrank[hh[c]];
-    }
+    if (jj[c] >= 0) slot[base[c >> 1] + lane + 64 * (c & 1)] = hrank[hh[c]];
 }
 
-// uniq (at the entry offsets) -> tile_u (at the list offsets)
-__global__ void __launch_bounds__(kTileThreads) k_tile_compact(const int64_t *__restrict__ ent_off,
-                                                               const int64_t *__restrict__ u_off,
-                                                               const int32_t *__restrict__ uniq,
-                                                               int32_t *__restrict__ tile_u) {
-  const int64_t t = blockIdx.x;
-  const int64_t a = ent_off[t], b = u_off[t], m = u_off[t + 1] - b;
-  for (int64_t s = threadIdx.x; s < m; s += kTileThreads) tile_u[b + s] = uniq[a + s];
+// uniq (kTileEntries places per tile) -> tile_u (at the list offsets), a wave per tile
+__global__ void __launch_bounds__(kBlock) k_tile_compact(const int64_t *__restrict__ u_off,
+                                                         const int32_t *__restrict__ uniq, int64_t nt,
+                                                         int32_t *__restrict__ tile_u) {
+  const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (t >= nt) return;
+  const int64_t b = u_off[t], m = u_off[t + 1] - b;
+#pragma unroll 4
+  for (int64_t s = threadIdx.x & 63; s < m; s += 64) tile_u[b + s] = uniq[kTileEntries * t + s];
 }
 
 // reverse-edge map: rev[k] = position of (j, i) in row j for entry k = (i, j)
@@ -1382,25 +1367,19 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   if (!take(nb, nb->slot, nb->nnz + kQuadPad) || !take(nb, nb->tile_off, nt + 1))
     return set_error(ctx, GF_ENOMEM, "neighbour tile allocation failed");
   Arena ar;
-  std::vector<size_t> sz = {sizeof(int32_t) * nt, sizeof(int64_t) * (nt + 1), sizeof(int64_t) * scan_tmp_elems(nt + 1),
-                            sizeof(int32_t) * std::max<int64_t>(nb->nnz, 1), sizeof(int32_t) * nt, 64};
+  std::vector<size_t> sz = {sizeof(int64_t) * scan_tmp_elems(nt + 1), sizeof(int32_t) * kTileEntries * (size_t)nt,
+                            sizeof(int32_t) * nt, 64};
   gf_status st;
   if ((st = ensure_scratch(ctx, arena_bytes(sz), &ar))) return st;
-  int32_t *ent = ar.take<int32_t>(nt);
-  int64_t *ent_off = ar.take<int64_t>(nt + 1);
   int64_t *tmp64 = ar.take<int64_t>(scan_tmp_elems(nt + 1));
-  int32_t *uniq = ar.take<int32_t>(std::max<int64_t>(nb->nnz, 1));
+  int32_t *uniq = ar.take<int32_t>(kTileEntries * (size_t)nt);
   int32_t *cnt = ar.take<int32_t>(nt);
   int32_t *grp_max = ar.take<int32_t>(16);
   {
     ProfScope prof(ctx, "nbr_tile_unique");
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kBlock), 0, sm, grp_max, (int64_t)16, 0);
-    hipLaunchKernelGGL(k_tile_entries, dim3(grid_for(nt, kBlock)), dim3(kBlock), 0, sm, tg, nb->row_ptr, nb->grouped,
-                       ent);
-    GF_LAUNCH_CHECK(ctx);
-    if ((st = scan_i32_to_i64(ctx, ent, ent_off, nt, tmp64))) return st;
     hipLaunchKernelGGL(k_tile_unique, dim3((unsigned)nt), dim3(kTileThreads), 0, sm, tg, nb->row_ptr, nb->col,
-                       nb->grouped, ent_off, nb->slot, uniq, cnt, grp_max);
+                       nb->grouped, nb->slot, uniq, cnt, grp_max);
     GF_LAUNCH_CHECK(ctx);
     if ((st = scan_i32_to_i64(ctx, cnt, nb->tile_off, nt, tmp64))) return st;
   }
@@ -1413,7 +1392,7 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   if (!take(nb, nb->tile_u, total))
     return set_error(ctx, GF_ENOMEM, "neighbour tile list allocation failed");
   ProfScope prof(ctx, "nbr_tile_compact");
-  hipLaunchKernelGGL(k_tile_compact, dim3((unsigned)nt), dim3(kTileThreads), 0, sm, ent_off, nb->tile_off, uniq,
+  hipLaunchKernelGGL(k_tile_compact, dim3(grid_for(nt, kBlock / 64)), dim3(kBlock), 0, sm, nb->tile_off, uniq, nt,
                      nb->tile_u);
   GF_LAUNCH_CHECK(ctx);
   return GF_OK;
