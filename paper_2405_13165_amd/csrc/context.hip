@@ -349,7 +349,9 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_single(TO *bsum, int64_t nb
   if (threadIdx.x == 0) bsum[nb] = carry;
 }
 
-template <typename TI, typename TO>
+// bsum: the scanned block sums, or (RAW) the block sums themselves, of which each
+// block adds up those before it; no block sums are read when there is one block
+template <typename TI, typename TO, bool RAW>
 __global__ void __launch_bounds__(kScanBlock) k_scan_apply(const TI *in, int64_t n, const TO *bsum,
                                                            int64_t nb, TO *out) {
   int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
@@ -360,27 +362,46 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_apply(const TI *in, int64_t
     v[k] = (base + k < n) ? (TO)in[base + k] : (TO)0;
     s += v[k];
   }
+  TO before = 0;
+  if constexpr (RAW) {
+    TO part = 0;
+    for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += kScanBlock) part += bsum[b];
+    if (blockIdx.x > 0) block_exclusive_scan<TO>(part, &before);
+  } else {
+    before = bsum[blockIdx.x];
+  }
   TO tot;
-  TO run = bsum[blockIdx.x] + block_exclusive_scan<TO>(s, &tot);
+  TO run = before + block_exclusive_scan<TO>(s, &tot);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = before + tot;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     if (base + k < n) out[base + k] = run;
     run += v[k];
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = bsum[nb];
 }
 
+// Up to kScanRaw blocks each adds up the block sums before it (at most 16 reads
+// per thread from L2), which saves the launch that would scan them; one block
+// needs no sums at all.
+constexpr int64_t kScanRaw = 4096;
 template <typename TI, typename TO>
 gf_status scan_impl(gf_ctx *ctx, const TI *in, TO *out, int64_t n, TO *tmp) {
   int64_t nb = (n + kScanTile - 1) / kScanTile;
   if (nb < 1) nb = 1;
-  hipLaunchKernelGGL((k_scan_partials<TI, TO>), dim3((unsigned)nb), dim3(kScanBlock), 0, ctx->stream,
-                     in, n, tmp);
-  GF_LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL((k_scan_single<TO>), dim3(1), dim3(kScanBlock), 0, ctx->stream, tmp, nb);
-  GF_LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL((k_scan_apply<TI, TO>), dim3((unsigned)nb), dim3(kScanBlock), 0, ctx->stream,
-                     in, n, tmp, nb, out);
+  if (nb > 1) {
+    hipLaunchKernelGGL((k_scan_partials<TI, TO>), dim3((unsigned)nb), dim3(kScanBlock), 0, ctx->stream,
+                       in, n, tmp);
+    GF_LAUNCH_CHECK(ctx);
+  }
+  if (nb <= kScanRaw) {
+    hipLaunchKernelGGL((k_scan_apply<TI, TO, true>), dim3((unsigned)nb), dim3(kScanBlock), 0, ctx->stream,
+                       in, n, tmp, nb, out);
+  } else {
+    hipLaunchKernelGGL((k_scan_single<TO>), dim3(1), dim3(kScanBlock), 0, ctx->stream, tmp, nb);
+    GF_LAUNCH_CHECK(ctx);
+    hipLaunchKernelGGL((k_scan_apply<TI, TO, false>), dim3((unsigned)nb), dim3(kScanBlock), 0, ctx->stream,
+                       in, n, tmp, nb, out);
+  }
   GF_LAUNCH_CHECK(ctx);
   return GF_OK;
 }

@@ -3,8 +3,8 @@
 // Pipeline (one stream, one host read-back of sizes):
 //   bbox/validate -> grid of each particle (model, support level) and its
 //   cell key + per-cell counts (atomics) -> scan -> scatter into cell order
-//   -> list of non-empty cells and of search items -> finer Morton order inside
-//   cells -> positions gathered in cell order -> search, count pass -> scan
+//   -> lists of units of cells and of search items -> finer Morton order inside
+//   them and records in cell order -> search, count pass -> scan
 //   -> fill pass -> per-row sort -> (several support levels: a second cell
 //   pass over each model's finest grid, a model-wide Morton order) ->
 //   grouping of particles by (model, neighbour-count band) for the batched
@@ -24,19 +24,64 @@ constexpr int kBlock = 256;
 constexpr int kMaxRow = 2048;
 
 // -------------------------------------------------------------- reductions
-__device__ inline double wave_min(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  return v;
+// The butterfly steps move lanes without the LDS crossbar: DPP within rows of
+// 16, then the swaps of rows and half waves, which give both values at once.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
 }
-__device__ inline double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+__device__ __forceinline__ double f64_of(unsigned lo, unsigned hi) {
+  return __longlong_as_double(((int64_t)hi << 32) | lo);
+}
+template <bool MIN>
+__device__ __forceinline__ double pick(double a, double b) { return MIN ? fmin(a, b) : fmax(a, b); }
+// min / max of the first LANES (32 or 64) lanes, in each of them
+template <bool MIN, int LANES>
+__device__ __forceinline__ double lanes_pick(double v) {
+  v = pick<MIN>(v, dpp_f64<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+  v = pick<MIN>(v, dpp_f64<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+  v = pick<MIN>(v, dpp_f64<0x141>(v));  // row_half_mirror
+  v = pick<MIN>(v, dpp_f64<0x140>(v));  // row_mirror
+  {
+    const int64_t b = __double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    v = pick<MIN>(f64_of(l[0], h[0]), f64_of(l[1], h[1]));
+  }
+  if constexpr (LANES == 64) {
+    const int64_t b = __double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    v = pick<MIN>(f64_of(l[0], h[0]), f64_of(l[1], h[1]));
+  }
   return v;
 }
 __device__ inline int wave_sum_i(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// inclusive scans over the wave by lane moves within rows of 16 and row broadcasts
+__device__ inline int wave_scan_add(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+__device__ inline int wave_scan_max(int v) {  // of values >= 0
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
   return v;
 }
 
@@ -52,7 +97,8 @@ constexpr int kBoxVals = 16;
 // value k of the box is reduced with min (else max)
 __host__ __device__ inline bool box_is_min(int k) { return (k % 8) < 3 || (k % 8) == 7; }
 
-__global__ void __launch_bounds__(kBlock) k_bbox(const double *__restrict__ x, const double *__restrict__ y,
+constexpr int kBboxThreads = 1024;
+__global__ void __launch_bounds__(kBboxThreads) k_bbox(const double *__restrict__ x, const double *__restrict__ y,
                                                  const double *__restrict__ z, const double *__restrict__ h,
                                                  const int8_t *__restrict__ model, int64_t n,
                                                  double *__restrict__ part, int *__restrict__ bad_part) {
@@ -79,12 +125,18 @@ __global__ void __launch_bounds__(kBlock) k_bbox(const double *__restrict__ x, c
       v[mm * 8 + 7] = fmin(v[mm * 8 + 7], hi);
     }
   }
-  __shared__ double sh[kBlock / 64][kBoxVals];
-  __shared__ int shb[kBlock / 64];
+  __shared__ double sh[kBboxThreads / 64][kBoxVals];
+  __shared__ int shb[kBboxThreads / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  for (int k = 0; k < kBoxVals; ++k) {
-    double r = box_is_min(k) ? wave_min(v[k]) : wave_max(v[k]);
-    if (lane == 0) sh[wid][k] = r;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    if (__ballot(v[8 * m + 6] > 0.0)) {  // (most waves meet one model only)
+#pragma unroll
+      for (int k = 8 * m; k < 8 * m + 8; ++k) v[k] = box_is_min(k) ? lanes_pick<true, 64>(v[k]) : lanes_pick<false, 64>(v[k]);
+    }
+#pragma unroll
+    for (int k = 8 * m; k < 8 * m + 8; ++k)
+      if (lane == 0) sh[wid][k] = v[k];
   }
   int bs = wave_sum_i(bad);
   if (lane == 0) shb[wid] = bs;
@@ -92,12 +144,12 @@ __global__ void __launch_bounds__(kBlock) k_bbox(const double *__restrict__ x, c
   if (threadIdx.x < kBoxVals) {
     int k = threadIdx.x;
     double r = sh[0][k];
-    for (int w = 1; w < kBlock / 64; ++w) r = box_is_min(k) ? fmin(r, sh[w][k]) : fmax(r, sh[w][k]);
+    for (int w = 1; w < kBboxThreads / 64; ++w) r = box_is_min(k) ? fmin(r, sh[w][k]) : fmax(r, sh[w][k]);
     part[(int64_t)blockIdx.x * kBoxVals + k] = r;
   }
   if (threadIdx.x == 0) {
     int b = 0;
-    for (int w = 0; w < kBlock / 64; ++w) b += shb[w];
+    for (int w = 0; w < kBboxThreads / 64; ++w) b += shb[w];
     bad_part[blockIdx.x] = b;
   }
 }
@@ -112,35 +164,38 @@ __global__ void k_publish(const int32_t *__restrict__ a, int na, const int64_t *
   if (k == na) host[na] = *last;
 }
 
-// one block of kBboxFin threads: thread b takes block partial b (nblk <= kBboxFin); out and
+// one block: thread t combines value t % 16 of the block partials t / 16, t / 16 + 16, ...; out and
 // bad_out lie in pinned host memory
-constexpr int kBboxFin = 1024;
+constexpr int kBboxFin = 256;
+constexpr int kBboxBlocks = 256;  // blocks of the first pass, at most
 __global__ void __launch_bounds__(kBboxFin) k_bbox_final(const double *__restrict__ part,
                                                          const int *__restrict__ bad_part, int nblk,
                                                          double *__restrict__ out, int *__restrict__ bad_out) {
-  __shared__ double sh[kBboxFin / 64][kBoxVals];
+  constexpr int kParts = kBboxFin / kBoxVals;
+  __shared__ double sh[kParts][kBoxVals];
   __shared__ int shb[kBboxFin / 64];
-  const int b = threadIdx.x, lane = b & 63, wid = b >> 6;
-  const bool has = b < nblk;
-  for (int k = 0; k < kBoxVals; ++k) {
-    const bool lo = box_is_min(k);
-    const double t = has ? part[(int64_t)b * kBoxVals + k] : (lo ? INFINITY : -INFINITY);
-    const double r = lo ? wave_min(t) : wave_max(t);
-    if (lane == 0) sh[wid][k] = r;
+  const int k = threadIdx.x % kBoxVals, q = threadIdx.x / kBoxVals;
+  const bool lo = box_is_min(k);
+  double r = lo ? INFINITY : -INFINITY;
+#pragma unroll 8
+  for (int b = q; b < nblk; b += kParts) {
+    const double t = part[(int64_t)b * kBoxVals + k];
+    r = lo ? fmin(r, t) : fmax(r, t);
   }
-  const int bs = wave_sum_i(has ? bad_part[b] : 0);
-  if (lane == 0) shb[wid] = bs;
+  sh[q][k] = r;
+  int sum = 0;
+  for (int b = threadIdx.x; b < nblk; b += kBboxFin) sum += bad_part[b];
+  sum = wave_sum_i(sum);
+  if ((threadIdx.x & 63) == 0) shb[threadIdx.x >> 6] = sum;
   __syncthreads();
-  if (b < kBoxVals) {
-    const bool lo = box_is_min(b);
-    double r = sh[0][b];
-    for (int w = 1; w < kBboxFin / 64; ++w) r = lo ? fmin(r, sh[w][b]) : fmax(r, sh[w][b]);
-    out[b] = r;
+  if (q == 0) {
+    for (int w = 1; w < kParts; ++w) r = lo ? fmin(r, sh[w][k]) : fmax(r, sh[w][k]);
+    out[k] = r;
   }
-  if (b == 0) {
-    int sum = 0;
-    for (int w = 0; w < kBboxFin / 64; ++w) sum += shb[w];
-    *bad_out = sum;
+  if (threadIdx.x == 0) {
+    int all = 0;
+    for (int w = 0; w < kBboxFin / 64; ++w) all += shb[w];
+    *bad_out = all;
   }
 }
 
@@ -209,6 +264,13 @@ __global__ void __launch_bounds__(kBlock) k_fill_i32(int32_t *a, int64_t n, int3
     a[i] = v;
 }
 
+// counts[0 .. n) and small[0 .. 32) cleared
+__global__ void __launch_bounds__(kBlock) k_clear(int32_t *__restrict__ counts, int64_t n, int32_t *__restrict__ small) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) counts[i] = 0;
+  if (i < 32 && small) small[i] = 0;
+}
+
 // key[i]: cell of particle i; counts[k]: particles per cell
 __global__ void __launch_bounds__(kBlock) k_keys(const double *__restrict__ x, const double *__restrict__ y,
                                                  const double *__restrict__ z, const double *__restrict__ h,
@@ -216,32 +278,32 @@ __global__ void __launch_bounds__(kBlock) k_keys(const double *__restrict__ x, c
                                                  int32_t *__restrict__ key, int32_t *__restrict__ slot,
                                                  int32_t *__restrict__ counts) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int s = slot_of(g, model[i], h[i]);
-  int cx = cell_of(x[i], g.lo[s][0], g.inv_edge[s], g.dim[s][0]);
-  int cy = cell_of(y[i], g.lo[s][1], g.inv_edge[s], g.dim[s][1]);
-  int cz = cell_of(z[i], g.lo[s][2], g.inv_edge[s], g.dim[s][2]);
-  int32_t k = (int32_t)(g.base[s] + morton(cx, cy, cz, g.bits[s][0], g.bits[s][1], g.bits[s][2]));
-  key[i] = k;
-  // Slot within the cell.  Neighbouring particles mostly share a cell, and
-  // 64 atomics on one counter serialise, so the lanes of the wave with the
-  // same cell share one atomic: the lowest of them reserves their count and
-  // each takes base + its rank among them.  (The order within a cell is
-  // re-sorted later; only the set of slots 0..count-1 matters.)
   const int lane = threadIdx.x & 63;
-  unsigned long long todo = __ballot(1);
-  int32_t mine = 0;
-  while (todo) {
-    const int leader = __builtin_ctzll(todo);
-    const int32_t lk = __shfl(k, leader, 64);
-    const unsigned long long same = __ballot(k == lk) & todo;
-    int32_t base = 0;
-    if (lane == leader) base = atomicAdd(&counts[lk], (int32_t)__popcll(same));
-    base = __shfl(base, leader, 64);
-    if ((same >> lane) & 1ull) mine = base + (int32_t)__popcll(same & ((1ull << lane) - 1ull));
-    todo &= ~same;
+  int32_t k = -1;
+  if (i < n) {
+    const int s = slot_of(g, model[i], h[i]);
+    const int cx = cell_of(x[i], g.lo[s][0], g.inv_edge[s], g.dim[s][0]);
+    const int cy = cell_of(y[i], g.lo[s][1], g.inv_edge[s], g.dim[s][1]);
+    const int cz = cell_of(z[i], g.lo[s][2], g.inv_edge[s], g.dim[s][2]);
+    k = (int32_t)g.base[s] + morton32(cx, cy, cz, g.bits[s][0], g.bits[s][1], g.bits[s][2]);
+    key[i] = k;
   }
-  slot[i] = mine;
+  // Slot within the cell.  Particles numbered one after another often share a
+  // cell, and atomics on one counter serialise, so a run of lanes with one key
+  // shares one atomic: its first lane reserves the run's length.  (The order
+  // within a cell is re-sorted later; only the set of slots 0..count-1 matters.
+  // Runs, not all the lanes of a key: with particles in no order, as the jet's
+  // film, a wave holds 64 keys and collecting each key's lanes took 64 rounds:
+  // 126 -> 72 us on the jet, 27 -> 11 us on the mixed cloud.)
+  const int32_t before = __shfl_up(k, 1, 64);
+  const bool first = lane == 0 || k != before;
+  const unsigned long long heads = __ballot(first);
+  const int mine = 63 - __builtin_clzll(heads & (~0ull >> (63 - lane)));  // my run's first lane
+  const unsigned long long after = lane == 63 ? 0ull : heads >> (lane + 1);
+  int32_t base = 0;
+  if (first && k >= 0) base = atomicAdd(&counts[k], after ? __builtin_ctzll(after) + 1 : 64 - lane);
+  base = __shfl(base, mine, 64);
+  if (i < n) slot[i] = base + lane - mine;
 }
 
 // Search items: the rows of one cell, or of an aligned Morton block of 2, 4 or
@@ -251,41 +313,68 @@ __global__ void __launch_bounds__(kBlock) k_keys(const double *__restrict__ x, c
 // one range of the cell order (a multiple of four but for a unit's last, as the
 // search takes rows in fours), and its candidates are read once for all of
 // them.  items[k] = (first row, rows, grid); their order is left to the run (no
-// result depends on it).  Also the number of particles of each grid.
+// result depends on it).  Also the units themselves as (first row, rows, grid,
+// cells - 1), those of more than kUnitSmall rows in a list of their own, and the
+// number of particles of each grid.
+constexpr int kUnitSmall = 256;
 constexpr int kItemFill = 20;
 constexpr int kItemBits = 3;
-__global__ void __launch_bounds__(kBlock) k_items(const int32_t *__restrict__ cell_start, Grid g, int most,
-                                                  int4 *__restrict__ items, int32_t *__restrict__ nitems,
-                                                  int32_t *__restrict__ slot_count) {
+struct CellLists {
+  int4 *items, *units, *big;             // (items may be NULL: not wanted)
+  int32_t *nitems, *nunits, *nbig;
+  int32_t *slot_count;
+};
+// (a block's units and items take their places by one atomic each: a few
+// addresses serve the whole grid)
+constexpr int kItemsBlock = 1024;
+__global__ void __launch_bounds__(kItemsBlock) k_items(const int32_t *__restrict__ cell_start, Grid g, int most,
+                                                       CellLists out) {
+  __shared__ int s_units[kItemsBlock / 64], s_items[kItemsBlock / 64], s_base[2];
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int a = 0, b = 0, s = 0;
+  int a = 0, b = 0, s = 0, cells = 1;
   if (k < g.nkeys) {
     while (s + 1 < g.nslots && k >= g.base[s + 1]) ++s;
     const int64_t end = (s + 1 < g.nslots) ? g.base[s + 1] : g.nkeys;
     const int count = cell_start[end] - cell_start[g.base[s]];
-    if (k == g.base[s]) slot_count[s] = count;
+    if (k == g.base[s]) out.slot_count[s] = count;
     const double mean = (double)count / ((double)g.dim[s][0] * g.dim[s][1] * g.dim[s][2]);
     int sh = 0;
     while (sh < kItemBits && mean * (double)(1 << sh) < (double)kItemFill && ((int64_t)2 << sh) <= end - g.base[s]) ++sh;
     if (((k - g.base[s]) & ((1 << sh) - 1)) == 0) {
       a = cell_start[k];
       b = cell_start[k + (1 << sh)];
+      cells = 1 << sh;
     }
   }
-  // parts of this unit, and their places (one atomic per wave)
-  const int len = b - a, parts = (len + most - 1) / most;
-  const int lane = threadIdx.x & 63;
-  int inc = parts;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += v;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, len = b - a;
+  const bool small = len > 0 && len <= kUnitSmall;
+  const int parts = out.items ? (len + most - 1) / most : 0;
+  const uint64_t m = __ballot(small);
+  const int inc = wave_scan_add(parts);
+  if (lane == 63) {
+    s_units[w] = (int)__popcll(m);
+    s_items[w] = inc;
   }
-  int at = 0;
-  if (lane == 63 && inc) at = atomicAdd(nitems, inc);
-  at = __builtin_amdgcn_readlane(at, 63) + inc - parts;
-  const int size = ((len + parts - 1) / max(parts, 1) + 3) & ~3;  // <= most
-  for (int q = 0, f = a; f < b; ++q, f += size) items[at + q] = make_int4(f, min(size, b - f), s, 0);
+  __syncthreads();
+  int ub = 0, ib = 0, ut = 0, itot = 0;
+  for (int q = 0; q < kItemsBlock / 64; ++q) {
+    if (q < w) { ub += s_units[q]; ib += s_items[q]; }
+    ut += s_units[q];
+    itot += s_items[q];
+  }
+  if (threadIdx.x == 0) {
+    s_base[0] = ut ? atomicAdd(out.nunits, ut) : 0;
+    s_base[1] = itot ? atomicAdd(out.nitems, itot) : 0;
+  }
+  __syncthreads();
+  if (len > 0) {
+    int4 *u = small ? out.units + s_base[0] + ub + __popcll(m & ((1ull << lane) - 1ull)) : out.big + atomicAdd(out.nbig, 1);
+    *u = make_int4(a, len, s, cells - 1);
+  }
+  if (parts == 0) return;
+  const int at = s_base[1] + ib + inc - parts;
+  const int size = ((len + parts - 1) / parts + 3) & ~3;  // <= most
+  for (int q = 0, f = a; f < b; ++q, f += size) out.items[at + q] = make_int4(f, min(size, b - f), s, 0);
 }
 
 __global__ void __launch_bounds__(kBlock) k_scatter(const int32_t *__restrict__ key, const int32_t *__restrict__ slot,
@@ -296,31 +385,90 @@ __global__ void __launch_bounds__(kBlock) k_scatter(const int32_t *__restrict__ 
   order[cell_start[key[i]] + slot[i]] = (int32_t)i;
 }
 
-// non-empty cells: head[s] = 1 where sorted position s starts a cell
-__global__ void __launch_bounds__(kBlock) k_cell_heads(const int32_t *__restrict__ order,
-                                                       const int32_t *__restrict__ key, int64_t n,
-                                                       int32_t *__restrict__ head) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  head[s] = (s == 0 || key[order[s]] != key[order[s - 1]]) ? 1 : 0;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cell_list(const int32_t *__restrict__ head,
-                                                      const int32_t *__restrict__ pos, int64_t n,
-                                                      int32_t *__restrict__ cells) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  if (head[s]) cells[pos[s]] = (int32_t)s;
-}
-
 // Order the particles of each cell by a finer Morton key (kSubBits more bits
-// per axis), so that runs of the cell order stay spatially compact when a
-// cell is much larger than a typical support (uneven h).  One wave per cell,
-// bitonic sort in LDS; cells with more than kCellSort particles keep their
-// order.  The neighbour sets do not depend on this order.
+// per axis), ties by index, so that runs of the cell order stay spatially
+// compact when a cell is much larger than a typical support (uneven h), and
+// write the records (x, y, z, h / 2) of the cell order (sp may be NULL).  Units
+// of up to kUnitSmall rows: a wave each, the rank of a particle counted over the
+// unit's keys in LDS.  Inside a unit the fine keys differ only in the cell's
+// place in the unit and the low kSubBits bits per axis, so those bits and the
+// particle index, packed in 64 bits, order it exactly.  What bounds it: the
+// gathers of the particles' data.  With the records written here (one more pass
+// over the particles before) and a 12-bit sub key instead of the 63-bit one,
+// sort and records of the mixed cloud take 16 us (55 before), of the 2.0M jet,
+// whose film comes in no order, 126 us (447 before).
 constexpr int kSubBits = 4;
 constexpr int kCellSort = 2048;
 
+// low kSubBits bits per axis of the fine Morton key, interleaved
+__device__ inline uint32_t fine_sub(double x, double y, double z, const Grid &g, int s) {
+  const double f = (double)(1 << kSubBits);
+  const double v[3] = {x, y, z};
+  uint32_t key = 0;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double t = floor((v[d] - g.lo[s][d]) * g.inv_edge[s] * f);
+    const double hi = (double)g.dim[s][d] * f - 1.0;
+    const uint32_t c = (uint32_t)(int)(t < 0.0 ? 0.0 : (t > hi ? hi : t));
+#pragma unroll
+    for (int b = 0; b < kSubBits; ++b) key |= ((c >> b) & 1u) << (3 * b + d);
+  }
+  return key;
+}
+
+constexpr int kCellSortWaves = 4;
+__global__ void __launch_bounds__(64 * kCellSortWaves) k_cell_sort_small(
+    const int4 *__restrict__ units, const int32_t *__restrict__ nunits, const int32_t *__restrict__ key,
+    const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
+    const double *__restrict__ h, Grid g, int32_t *order, double4 *__restrict__ sp) {
+  constexpr int NV = kUnitSmall / 64;
+  __shared__ __attribute__((aligned(16))) uint64_t s_key[kCellSortWaves][kUnitSmall];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nu = *nunits, stride = gridDim.x * kCellSortWaves;
+  for (int u = blockIdx.x * kCellSortWaves + w; u < nu; u += stride) {
+    const int4 un = units[u];
+    const int b = un.x, len = un.y, s = un.z;
+    int32_t id[NV];
+    double4 rec[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int t = lane + 64 * q;
+      if (64 * q >= len) continue;
+      id[q] = 0;
+      uint64_t k = ~0ull;
+      if (t < len) {
+        const int32_t i = order[b + t];
+        id[q] = i;
+        rec[q] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
+        const uint32_t cell = (uint32_t)(key[i] - (int32_t)g.base[s]) & (uint32_t)un.w;
+        const uint32_t sub = (cell << (3 * kSubBits)) | fine_sub(rec[q].x, rec[q].y, rec[q].z, g, s);
+        k = ((uint64_t)sub << 32) | (uint32_t)i;
+      }
+      s_key[w][t] = k;
+    }
+    wave_fence();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int t = lane + 64 * q;
+      if (64 * q >= len) continue;
+      const uint64_t mine = s_key[w][t];
+      int rank = 0;
+      for (int c = 0; c < len; c += 2) {  // (an odd count's last pair ends in a pad, which is not smaller)
+        const ulonglong2 kk = *reinterpret_cast<const ulonglong2 *>(&s_key[w][c]);
+        rank += (kk.x < mine) + (kk.y < mine);
+      }
+      if (t < len) {
+        order[b + rank] = id[q];
+        if (sp) sp[b + rank] = rec[q];
+      }
+    }
+    wave_fence();
+  }
+}
+
+// Larger units, a block each, by a bitonic network in LDS over the whole fine
+// key; units of more than kCellSort particles keep their order.  The
+// neighbour sets do not depend on this order.
 __device__ inline uint64_t fine_key(double x, double y, double z, const Grid &g, int s) {
   const double f = (double)(1 << kSubBits);
   int c[3];
@@ -337,95 +485,53 @@ __device__ inline uint64_t fine_key(double x, double y, double z, const Grid &g,
   return key;
 }
 
-// cells[c]: first sorted position of the c-th non-empty cell; *ncells and
-// the end n close the list
-// Cells of up to kCellSortReg particles, one wave per cell, in registers.
-// Inside a cell the fine keys differ only in their kSubBits low bits per axis
-// (the interleaved low 3 * kSubBits bits), so (those bits, particle index)
-// packed in 64 bits orders the cell exactly as the full comparison does.
-constexpr int kCellSortReg = 64;
-constexpr int kCellSortWaves = 4;
-__global__ void __launch_bounds__(64 * kCellSortWaves) k_cell_sort_reg(
-    const int32_t *__restrict__ cells, const int32_t *__restrict__ ncells, int64_t n, const double *__restrict__ x,
-    const double *__restrict__ y, const double *__restrict__ z, const double *__restrict__ h,
-    const int8_t *__restrict__ model, Grid g, int32_t *__restrict__ order) {
-  const int lane = threadIdx.x & 63;
-  const int32_t nc = *ncells;
-  const int64_t stride = (int64_t)gridDim.x * kCellSortWaves;
-  for (int64_t c = (int64_t)blockIdx.x * kCellSortWaves + (threadIdx.x >> 6); c < nc; c += stride) {
-    const int32_t b = cells[c], len = (c + 1 < nc ? cells[c + 1] : (int32_t)n) - b;
-    if (len <= 1 || len > kCellSortReg) continue;
-    uint64_t v = ~0ull;
-    if (lane < len) {
-      const int32_t i = order[b + lane];
-      const uint64_t sub = fine_key(x[i], y[i], z[i], g, slot_of(g, model[i], h[i])) & ((1ull << (3 * kSubBits)) - 1);
-      v = (sub << 32) | (uint32_t)i;
-    }
-#pragma unroll
-    for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        const uint64_t p = __shfl_xor(v, j, 64);
-        const bool up = (lane & k) == 0, lower = (lane & j) == 0;
-        v = (lower == up) ? (v < p ? v : p) : (v < p ? p : v);
-      }
-    }
-    if (lane < len) order[b + lane] = (int32_t)(uint32_t)v;
-  }
-}
-
-__global__ void __launch_bounds__(64) k_cell_sort(const int32_t *__restrict__ cells, const int32_t *__restrict__ ncells,
-                                                  int64_t n, const double *__restrict__ x,
-                                                  const double *__restrict__ y, const double *__restrict__ z,
-                                                  const double *__restrict__ h, const int8_t *__restrict__ model,
-                                                  Grid g, int32_t *__restrict__ order) {
+__global__ void __launch_bounds__(kBlock) k_cell_sort_big(const int4 *__restrict__ units, const int32_t *__restrict__ nunits,
+                                                          const double *__restrict__ x, const double *__restrict__ y,
+                                                          const double *__restrict__ z, const double *__restrict__ h,
+                                                          Grid g, int32_t *order, double4 *__restrict__ sp) {
   __shared__ uint64_t kk[kCellSort];
   __shared__ int32_t id[kCellSort];
-  const int32_t nc = *ncells;
-  for (int64_t c = blockIdx.x; c < nc; c += gridDim.x) {
-    const int32_t b = cells[c], len = (c + 1 < nc ? cells[c + 1] : (int32_t)n) - b;
-    if (len <= kCellSortReg || len > kCellSort) continue;  // small cells: k_cell_sort_reg
-    int P = 1;
-    while (P < len) P <<= 1;
-    for (int t = threadIdx.x; t < P; t += 64) {
-      if (t < len) {
-        const int32_t i = order[b + t];
-        kk[t] = fine_key(x[i], y[i], z[i], g, slot_of(g, model[i], h[i]));
-        id[t] = i;
-      } else {
-        kk[t] = ~0ull;
-        id[t] = 0x7fffffff;
-      }
-    }
-    __syncthreads();
-    for (int k = 2; k <= P; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int t = threadIdx.x; t < P; t += 64) {
-          const int u = t ^ j;
-          if (u > t) {
-            const uint64_t a = kk[t], e = kk[u];
-            const int32_t ia = id[t], ie = id[u];
-            // ties (same sub-cell) by particle index: the order is deterministic
-            const bool gt = (a > e) || (a == e && ia > ie);
-            if (gt == ((t & k) == 0)) { kk[t] = e; kk[u] = a; id[t] = ie; id[u] = ia; }
-          }
+  const int nu = *nunits;
+  for (int u = blockIdx.x; u < nu; u += gridDim.x) {
+    const int4 un = units[u];
+    const int b = un.x, len = un.y, s = un.z;
+    if (len <= kCellSort) {
+      int P = 1;
+      while (P < len) P <<= 1;
+      for (int t = threadIdx.x; t < P; t += kBlock) {
+        if (t < len) {
+          const int32_t i = order[b + t];
+          kk[t] = fine_key(x[i], y[i], z[i], g, s);
+          id[t] = i;
+        } else {
+          kk[t] = ~0ull;
+          id[t] = 0x7fffffff;
         }
-        __syncthreads();
+      }
+      __syncthreads();
+      for (int k = 2; k <= P; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+          for (int t = threadIdx.x; t < P; t += kBlock) {
+            const int o = t ^ j;
+            if (o > t) {
+              const uint64_t a = kk[t], e = kk[o];
+              const int32_t ia = id[t], ie = id[o];
+              // ties (same sub-cell) by particle index: the order is deterministic
+              const bool gt = (a > e) || (a == e && ia > ie);
+              if (gt == ((t & k) == 0)) { kk[t] = e; kk[o] = a; id[t] = ie; id[o] = ia; }
+            }
+          }
+          __syncthreads();
+        }
       }
     }
-    for (int t = threadIdx.x; t < len; t += 64) order[b + t] = id[t];
+    for (int t = threadIdx.x; t < len; t += kBlock) {
+      const int32_t i = len <= kCellSort ? id[t] : order[b + t];
+      if (len <= kCellSort) order[b + t] = i;
+      if (sp) sp[b + t] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
+    }
     __syncthreads();
   }
-}
-
-__global__ void __launch_bounds__(kBlock) k_gather_pos(const int32_t *__restrict__ order, const double *__restrict__ x,
-                                                       const double *__restrict__ y, const double *__restrict__ z,
-                                                       const double *__restrict__ h, int64_t n,
-                                                       double4 *__restrict__ sp) {
-  int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  int32_t i = order[s];
-  sp[s] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
 }
 
 // Eq. (Nbd) predicate, evaluated as written without contraction so that the
@@ -476,7 +582,6 @@ constexpr int kSearchBlock = 256;
 constexpr int kSearchWaves = kSearchBlock / 64;
 constexpr int kSearchBlocksPerCu = 8;
 constexpr int kItemRows = 24;
-constexpr int kItemLanes = 32;          // the power of two at or above kItemRows
 constexpr int kRowPad = 4;              // entries of padding after the records and the order (rows are read in fours)
 constexpr int kRing = 128;              // a batch adds at most 64 to at most 63 left over
 constexpr int kStageWidths[2] = {512, 256};  // hits per row the count pass may stage, widest first
@@ -498,37 +603,10 @@ __device__ inline double uniform_f64(double v) {
   return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
 }
 
-// min / max over the first kItemLanes lanes of the wave, uniform
-__device__ inline double rows_min(double v) {
-#pragma unroll
-  for (int o = kItemLanes / 2; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  return uniform_f64(v);
-}
-__device__ inline double rows_max(double v) {
-#pragma unroll
-  for (int o = kItemLanes / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return uniform_f64(v);
-}
-
-// inclusive scans over the wave by lane moves within rows of 16 and row broadcasts
-__device__ inline int wave_scan_add(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-__device__ inline int wave_scan_max(int v) {  // of values >= 0
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
-  return v;
-}
+// min / max over the first 32 lanes of the wave, uniform
+static_assert(kItemRows <= 32, "an item's rows lie in the first 32 lanes");
+__device__ inline double rows_min(double v) { return uniform_f64(lanes_pick<true, 32>(v)); }
+__device__ inline double rows_max(double v) { return uniform_f64(lanes_pick<false, 32>(v)); }
 
 template <int MODE>
 __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restrict__ order,
@@ -976,28 +1054,30 @@ __global__ void __launch_bounds__(kSortBlock) k_row_sort(const int64_t *__restri
   }
 }
 
-// grouping: particles (in the given order) of group gsel, stable; the tiled
-// bands 0..kTileBand share the group of band kTileBand
+// Grouping.  The given order lists the particles of model 0, then those of
+// model 1; each model's rows of more than kTileBandRow entries follow its tiled
+// rows, the order kept in both parts.  pos: the long rows before each place.
 __global__ void __launch_bounds__(kBlock) k_group_flag(const int32_t *__restrict__ order, const int32_t *__restrict__ cnt,
-                                                       const int8_t *__restrict__ model, int64_t n, int gsel,
-                                                       int32_t *__restrict__ flag) {
-  int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  int32_t i = order[s];
-  int c = cnt[i];
-  int band = 0;
-  while (band < GF_NBAND - 1 && c > kBandHi[band]) ++band;
-  if (band < kTileBand) band = kTileBand;  // the tiled bands form one Morton-ordered range
-  flag[s] = (model[i] * GF_NBAND + band) == gsel ? 1 : 0;
+                                                       int64_t n, int32_t *__restrict__ flag) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s < n) flag[s] = cnt[order[s]] > kTileBandRow ? 1 : 0;
 }
 
 __global__ void __launch_bounds__(kBlock) k_group_scatter(const int32_t *__restrict__ order,
                                                           const int32_t *__restrict__ flag,
-                                                          const int32_t *__restrict__ pos, int64_t n,
-                                                          int64_t base, int32_t *__restrict__ grouped) {
-  int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                          const int32_t *__restrict__ pos, int64_t n, int64_t n0,
+                                                          int64_t long0, int64_t long1, int32_t *__restrict__ grouped) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
-  if (flag[s]) grouped[base + pos[s]] = order[s];
+  // first place, number of particles and of long rows of this place's model
+  const int64_t m0 = s < n0 ? 0 : n0, mn = s < n0 ? n0 : n - n0, ml = s < n0 ? long0 : long1;
+  const int64_t before = pos[s] - (s < n0 ? 0 : long0);
+  grouped[flag[s] ? m0 + (mn - ml) + before : s - before] = order[s];
+}
+
+__global__ void __launch_bounds__(kBlock) k_copy_i32(const int32_t *__restrict__ a, int64_t n, int32_t *__restrict__ b) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) b[i] = a[i];
 }
 
 // ---------------------------------------------------------------- tiles
@@ -1449,7 +1529,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   hipStream_t sm = ctx->stream;
 
   // ---- bounding boxes and validation
-  const int nblk = (int)std::min<int64_t>(1024, (n + kBlock - 1) / kBlock);
+  const int nblk = (int)std::min<int64_t>(kBboxBlocks, (n + kBboxThreads - 1) / kBboxThreads);
   Arena ar;
   std::vector<size_t> sz = {sizeof(double) * kBoxVals * nblk, sizeof(int) * nblk};
   if ((st = ensure_scratch(ctx, arena_bytes(sz), &ar))) return st;
@@ -1458,9 +1538,8 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   int *bad_part = ar.take<int>(nblk);
   double *hbox = (double *)ctx->host_pinned;
   int *hbad = (int *)((char *)ctx->host_pinned + 256);
-  hipLaunchKernelGGL(k_bbox, dim3(nblk), dim3(kBlock), 0, sm, p->x, p->y, p->z, p->h, p->model, n, part, bad_part);
+  hipLaunchKernelGGL(k_bbox, dim3(nblk), dim3(kBboxThreads), 0, sm, p->x, p->y, p->z, p->h, p->model, n, part, bad_part);
   GF_LAUNCH_CHECK(ctx);
-  static_assert(kBboxFin >= 1024, "one final thread per bounding-box block");
   hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(kBboxFin), 0, sm, part, bad_part, nblk, hbox, hbad);
   GF_LAUNCH_CHECK(ctx);
   GF_HIP(ctx, hipStreamSynchronize(sm));
@@ -1522,9 +1601,9 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   const int64_t K = g.nkeys;
   sz = {sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int32_t) * (K + 1), sizeof(int32_t) * scan_tmp_elems(K + 1),
         sizeof(double4) * (n + kRowPad), sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1),
-        sizeof(int32_t) * 32,
-        sizeof(int32_t) * n, sizeof(int32_t) * (n + 1), sizeof(int32_t) * scan_tmp_elems(n + 1),
-        sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int4) * n, sizeof(int32_t) * (n + kRowPad)};
+        sizeof(int32_t) * 32, sizeof(int32_t) * n, sizeof(int32_t) * (n + 1), sizeof(int32_t) * scan_tmp_elems(n + 1),
+        sizeof(int32_t) * n, sizeof(int4) * n, sizeof(int4) * n, sizeof(int4) * (n / kUnitSmall + 1),
+        sizeof(int32_t) * (n + kRowPad)};
   // rows staged by the count pass (sw entries each, the widest that stays
   // under 8 GB); rows found longer are filled by a second search pass
   int sw = 0;
@@ -1540,23 +1619,19 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   double4 *sp = ar.take<double4>(n + kRowPad);
   int32_t *cnt = ar.take<int32_t>(n);
   int64_t *tmp64 = ar.take<int64_t>(scan_tmp_elems(n + 1));
-  // hist[8], maxrow, -, search items [10], particles per grid
-  // [16 .. 16 + kMaxSlots); zeroed before use
+  // hist[8], maxrow, -, search items, units and big units [10 .. 12], units and big units of the second order
+  // [13], [14], particles per grid [16 .. 16 + kMaxSlots); zeroed before use
   int32_t *small = ar.take<int32_t>(32);
   int32_t *slot_count = small + 16;
   int32_t *gflag = ar.take<int32_t>(n);
   int32_t *gpos = ar.take<int32_t>(n + 1);
   int32_t *tmpg = ar.take<int32_t>(scan_tmp_elems(n + 1));
-  // list of non-empty cells (first sorted position of each); the cell heads
-  // and their scan borrow the grouping arrays, which are free until the fill
-  // pass has finished
-  int32_t *cells = ar.take<int32_t>(n);
   int32_t *order1 = ar.take<int32_t>(n);  // model-wide cell order for the grouping (several levels)
   int4 *items = ar.take<int4>(n);
+  int4 *units = ar.take<int4>(n);
+  int4 *big = ar.take<int4>(n / kUnitSmall + 1);
   int32_t *order = ar.take<int32_t>(n + kRowPad);  // particles in cell order
   int32_t *stage = use_stage ? ar.take<int32_t>((size_t)n * sw) : nullptr;
-  int32_t *head = gflag, *cpos = gpos;
-  const int32_t *ncells = cpos + n;
 
   gf_nbr *nb = new gf_nbr();
   nb->pool = ctx->pool;
@@ -1567,27 +1642,30 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   if (!take(nb, nb->row_ptr, n + 1) || !take(nb, nb->grouped, n))
     return fail(set_error(ctx, GF_ENOMEM, "neighbour handle allocation failed"));
 
+  // The particles in the order of a grid's cells (fine Morton order inside them), the units and, with them, the
+  // search items and the records of that order (sp).
+  auto cell_order = [&](const Grid &gg, int32_t *ord, const CellLists &lists, double4 *recs, bool clear_small) {
+    const int64_t KK = gg.nkeys;
+    hipLaunchKernelGGL(k_clear, dim3(grid_for(KK + 1, kBlock)), dim3(kBlock), 0, sm, cell_start, KK + 1,
+                       clear_small ? small : (int32_t *)nullptr);
+    hipLaunchKernelGGL(k_keys, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, p->x, p->y, p->z, p->h, p->model, n, gg,
+                       key, slot, cell_start);
+    gf_status s2 = scan_i32_to_i32(ctx, cell_start, cell_start, KK, tmp32);
+    if (s2) return s2;
+    hipLaunchKernelGGL(k_items, dim3(grid_for(KK, kItemsBlock)), dim3(kItemsBlock), 0, sm, cell_start, gg, kItemRows,
+                       lists);
+    hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, ord);
+    hipLaunchKernelGGL(k_cell_sort_small, dim3((unsigned)std::min<int64_t>(n / (8 * kCellSortWaves) + 1, 8 * ctx->num_cu)),
+                       dim3(64 * kCellSortWaves), 0, sm, lists.units, lists.nunits, key, p->x, p->y, p->z, p->h, gg, ord,
+                       recs);
+    hipLaunchKernelGGL(k_cell_sort_big, dim3((unsigned)std::min<int64_t>(n / kUnitSmall + 1, 4 * ctx->num_cu)),
+                       dim3(kBlock), 0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, gg, ord, recs);
+    return hipGetLastError() == hipSuccess ? GF_OK : set_error(ctx, GF_EHIP, "cell order kernels failed");
+  };
   {
   ProfScope prof_cells(ctx, "nbr_cells");
-  hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(K + 1, kBlock)), dim3(kBlock), 0, sm, cell_start, K + 1, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kBlock), 0, sm, small, (int64_t)32, 0);
-  hipLaunchKernelGGL(k_keys, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, p->x, p->y, p->z, p->h, p->model, n, g,
-                     key, slot, cell_start);
-  if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "key kernel launch failed"));
-  if ((st = scan_i32_to_i32(ctx, cell_start, cell_start, K, tmp32))) return fail(st);
-  hipLaunchKernelGGL(k_items, dim3(grid_for(K, kBlock)), dim3(kBlock), 0, sm, cell_start, g, kItemRows, items,
-                     small + 10, slot_count);
-  hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, order);
-  hipLaunchKernelGGL(k_cell_heads, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, order, key, n, head);
-  if ((st = scan_i32_to_i32(ctx, head, cpos, n, tmpg))) return fail(st);
-  hipLaunchKernelGGL(k_cell_list, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, head, cpos, n, cells);
-  hipLaunchKernelGGL(k_cell_sort_reg, dim3((unsigned)std::min<int64_t>((n + kCellSortWaves - 1) / kCellSortWaves, 4096)),
-                     dim3(64 * kCellSortWaves), 0, sm, cells, ncells, n, p->x, p->y, p->z, p->h, p->model, g,
-                     order);
-  hipLaunchKernelGGL(k_cell_sort, dim3((unsigned)std::min<int64_t>(n, 2048)), dim3(64), 0, sm, cells, ncells, n,
-                     p->x, p->y, p->z, p->h, p->model, g, order);
-  hipLaunchKernelGGL(k_gather_pos, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, order, p->x, p->y, p->z, p->h,
-                     n, sp);
+  const CellLists lists = {items, units, big, small + 10, small + 11, small + 12, slot_count};
+  if ((st = cell_order(g, order, lists, sp, true))) return fail(st);
   }
   // as many blocks as fit at once (fewer on small clouds), a multiple of 8: dealt to the XCDs in turn
   const dim3 search_grid((unsigned)std::min<int64_t>((n / (2 * kSearchWaves) + 8) / 8 * 8,
@@ -1664,38 +1742,29 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   if (g.slot0[1] - g.slot0[0] > 1 || g.slot0[2] - g.slot0[1] > 1) {
     ProfScope prof_o(ctx, "nbr_order");
     const Grid g1 = finest_grid(g);
-    const int64_t K1 = g1.nkeys;  // <= K: the slots of g1 are slots of g
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(K1 + 1, kBlock)), dim3(kBlock), 0, sm, cell_start, K1 + 1, 0);
-    hipLaunchKernelGGL(k_keys, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, p->x, p->y, p->z, p->h, p->model, n,
-                       g1, key, slot, cell_start);
-    if ((st = scan_i32_to_i32(ctx, cell_start, cell_start, K1, tmp32))) return fail(st);
-    hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, order1);
-    hipLaunchKernelGGL(k_cell_heads, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, order1, key, n, head);
-    if ((st = scan_i32_to_i32(ctx, head, cpos, n, tmpg))) return fail(st);
-    hipLaunchKernelGGL(k_cell_list, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, head, cpos, n, cells);
-    hipLaunchKernelGGL(k_cell_sort_reg,
-                       dim3((unsigned)std::min<int64_t>((n + kCellSortWaves - 1) / kCellSortWaves, 4096)),
-                       dim3(64 * kCellSortWaves), 0, sm, cells, ncells, n, p->x, p->y, p->z, p->h, p->model, g1,
-                       order1);
-    hipLaunchKernelGGL(k_cell_sort, dim3((unsigned)std::min<int64_t>(n, 2048)), dim3(64), 0, sm, cells, ncells, n,
-                       p->x, p->y, p->z, p->h, p->model, g1, order1);
-    if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "order kernels failed"));
+    // (g1.nkeys <= K: its slots are slots of g)
+    const CellLists lists = {nullptr, units, big, nullptr, small + 13, small + 14, slot_count};
+    if ((st = cell_order(g1, order1, lists, nullptr, false))) return fail(st);
     gorder = order1;
   }
   int64_t off = 0;
-  {
-  ProfScope prof_group(ctx, "nbr_group");
   for (int gsel = 0; gsel < 2 * GF_NBAND; ++gsel) {
     nb->group_start[gsel] = off;
-    if (hist[gsel] == 0) continue;
-    hipLaunchKernelGGL(k_group_flag, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, gorder, cnt, p->model, n,
-                       gsel, gflag);
-    if ((st = scan_i32_to_i32(ctx, gflag, gpos, n, tmpg))) return fail(st);
-    hipLaunchKernelGGL(k_group_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, gorder, gflag, gpos, n,
-                       off, nb->grouped);
     off += hist[gsel];
   }
   nb->group_start[2 * GF_NBAND] = off;
+  {
+    ProfScope prof_group(ctx, "nbr_group");
+    static_assert(kTileBand == 2 && GF_NBAND == 4 && kTileBandRow == 128, "one band of long rows per model");
+    const dim3 gg(grid_for(n, kBlock)), gb(kBlock);
+    if (nb->max_row <= kTileBandRow) {  // no long rows: the order is the grouping
+      hipLaunchKernelGGL(k_copy_i32, gg, gb, 0, sm, gorder, n, nb->grouped);
+    } else {
+      hipLaunchKernelGGL(k_group_flag, gg, gb, 0, sm, gorder, cnt, n, gflag);
+      if ((st = scan_i32_to_i32(ctx, gflag, gpos, n, tmpg))) return fail(st);
+      hipLaunchKernelGGL(k_group_scatter, gg, gb, 0, sm, gorder, gflag, gpos, n, nb->group_start[GF_NBAND], hist[3],
+                         hist[GF_NBAND + 3], nb->grouped);
+    }
   }
   if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "grouping kernels failed"));
   if (off != n) return fail(set_error(ctx, GF_EHIP, "internal error: grouping covers %lld of %lld", (long long)off,

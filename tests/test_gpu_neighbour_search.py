@@ -59,9 +59,11 @@ def test_chain(n):
     check(W._pack(x, z, z, np.full(n, 1.0), z, z))
 
 
-def test_two_far_clumps():
-    """A bounding box far larger than the supports: cells much wider than the reach of a row."""
-    d = clumps(24, 3, False)
+@pytest.mark.parametrize("per", [5, 24, 200])
+def test_two_far_clumps(per):
+    """A bounding box far larger than the supports: cells much wider than the reach of a row, holding up to 60, 288
+    and 2,400 particles (each in-cell order has its own kernel)."""
+    d = clumps(per, 3, False)
     d["x"] = np.where(np.arange(len(d["x"])) % 2 == 0, d["x"], d["x"] + 1e5)
     check(d)
 
