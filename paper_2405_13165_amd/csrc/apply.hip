@@ -64,45 +64,129 @@ __global__ void __launch_bounds__(kBlock) k_apply(const int32_t *__restrict__ sc
   }
 }
 
+// A stencil record (four operators of one entry) as loaded, converted to
+// FP64 only where it is used: a conversion right after the load would wait
+// for it there.
+// NT: read past the caches (each line by one instruction only).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+template <typename WT>
+struct WRec;
+template <>
+struct WRec<float> {
+  f32x4 v;
+  template <bool NT = false>
+  __device__ inline void load(const void *w, int64_t k) {
+    const f32x4 *p = reinterpret_cast<const f32x4 *>(w) + k;
+    if constexpr (NT) v = __builtin_nontemporal_load(p);
+    else v = *p;
+  }
+  __device__ inline double get(int s) const { return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w; }
+};
+template <>
+struct WRec<double> {
+  f64x2 a, b;
+  template <bool NT = false>
+  __device__ inline void load(const void *w, int64_t k) {
+    const f64x2 *p = reinterpret_cast<const f64x2 *>(w) + 2 * k;
+    a = p[0];
+    b = p[1];
+  }
+  __device__ inline double get(int s) const { return s == 0 ? a.x : s == 1 ? a.y : s == 2 ? b.x : b.y; }
+};
+
 // Tiled application (rows of the tiled bands): one block per neighbour tile;
 // the field values of the tile's distinct neighbours are staged in LDS and
 // each entry reads its value through slot[] (2 bytes) instead of col[]
 // (4 bytes) plus a gather.  The diagonal entry contributes u_i - u_i = 0.
-template <int T, typename WT, typename IOT>
-__global__ void __launch_bounds__(kTileRows * T) k_apply_tile(const int32_t *__restrict__ sched, int64_t nrows,
-                                                              const int64_t *__restrict__ row_ptr,
+// A lane's first kApplyAhead stencil records and slots are requested before the
+// tile is staged, and each next group while the last one is used: the wait for
+// the chain tile offset -> list -> field values -> barrier then covers them too.
+// One launch takes the tiles of both models where their team sizes agree.
+//
+// A team starts at the aligned block of T entries at or below its row, so that
+// each step of 8 lanes reads whole 128-byte lines of FP32 records, once: rows
+// start anywhere, and lines read half by one step and half by the next do not
+// survive in L2 between the two when every CU keeps hundreds of rows in flight.
+//
+// What bounds it: HBM (18 bytes per entry with FP32 stencils).  Mixed cloud
+// (534 MB of stencils, four operators) 160 -> 141 us, at an eighth of that size
+// 23.6 -> 19.1 us; with four or seven records ahead 154 and 180 us, without the
+// aligned start 168 us.  NT (stencils beyond the Infinity Cache, FP32): 141
+// against 150 us, but 55 against 43 us at 200 MB, which stay cached between
+// calls; FP64 records, whose lines two instructions share, lose by it (270
+// against 250 us).
+struct ApplyTiles {
+  const int32_t *grouped;
+  int nranges;
+  int64_t tile0[2], ntiles[2];   // tiles of the ranges
+  int64_t row0[2], nrows[2];     // their rows of grouped[]
+  int cap;
+};
+constexpr int kApplyAhead = 2;
+constexpr double kApplyStream = 240e6;  // bytes of stencils above which they are streamed
+
+template <int T, typename WT, typename IOT, bool NT>
+__global__ void __launch_bounds__(kTileRows * T) k_apply_tile(ApplyTiles at, const int64_t *__restrict__ row_ptr,
                                                               const int32_t *__restrict__ col,
                                                               const uint16_t *__restrict__ slot,
                                                               const int64_t *__restrict__ toff,
-                                                              const int32_t *__restrict__ tu, int64_t tile0, int cap,
+                                                              const int32_t *__restrict__ tu,
                                                               const void *__restrict__ w, unsigned mask,
                                                               const IOT *__restrict__ u, IOT *__restrict__ out,
                                                               int64_t n) {
   extern __shared__ double s_u[];
-  const int64_t tl = xcd_block(blockIdx.x, gridDim.x);
+  constexpr int A = kApplyAhead;
+  // each range is cut into slices for the XCDs by itself (a 3D tile costs four film tiles); the first
+  // takes a multiple of eight blocks, so that the second starts at XCD 0 again
+  const unsigned n0 = ((unsigned)at.ntiles[0] + 7u) & ~7u;
+  const int m = blockIdx.x >= n0 ? 1 : 0;
+  const int64_t tm = m ? xcd_block(blockIdx.x - n0, gridDim.x - n0) : xcd_block(blockIdx.x, at.nranges == 2 ? n0 : gridDim.x);
+  if (tm >= at.ntiles[m]) return;  // (the whole block)
+  const int64_t tl = at.tile0[m] + tm;
   const int team = threadIdx.x / T, lane = threadIdx.x % T;
-  const int64_t r = tl * kTileRows + team;
+  const int64_t r = tm * kTileRows + team;
   // row prologue first: its loads overlap the staging below
-  const bool live = r < nrows;
-  const int32_t i = live ? sched[r] : 0;
+  const bool live = r < at.nrows[m];
+  const int32_t i = live ? at.grouped[at.row0[m] + r] : 0;
   const int64_t b = live ? row_ptr[i] : 0, e = live ? row_ptr[i + 1] : 0;
   const double ui = (double)u[i];
-  const int64_t u0 = toff[tile0 + tl];
-  const int cnt = (int)(toff[tile0 + tl + 1] - u0);
-  const bool staged = cnt <= cap;
+  WRec<WT> ra[A], rb[A];
+  uint16_t sa[A], sb[A];
+  auto fetch = [&](int64_t k, WRec<WT> (&rec)[A], uint16_t (&sl)[A]) {
+#pragma unroll
+    for (int q = 0; q < A; ++q)
+      if (k + q * T >= b && k + q * T < e) {
+        rec[q].template load<NT>(w, k + q * T);
+        sl[q] = slot[k + q * T];
+      }
+  };
+  const int64_t kb = (b & ~(int64_t)(T - 1)) + lane;
+  fetch(kb, ra, sa);
+  const int64_t u0 = toff[tl];
+  const int cnt = (int)(toff[tl + 1] - u0);
+  const bool staged = cnt <= at.cap;
   if (staged)
     for (int s = threadIdx.x; s < cnt; s += blockDim.x) s_u[s] = (double)u[tu[u0 + s]];
   __syncthreads();
   if (!live) return;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   if (staged) {
-#pragma unroll 4
-    for (int64_t k = b + lane; k < e; k += T) {
-      double c[4];
-      W4<WT>::load(w, k, c);
-      const double du = s_u[slot[k]] - ui;
+    auto use = [&](int64_t k, const WRec<WT> (&rec)[A], const uint16_t (&sl)[A]) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) acc[s] += c[s] * du;
+      for (int q = 0; q < A; ++q)
+        if (k + q * T >= b && k + q * T < e) {
+          const double du = s_u[sl[q]] - ui;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc[s] += rec[q].get(s) * du;
+        }
+    };
+#pragma unroll 1
+    for (int64_t k = kb; k < e; k += 2 * A * T) {
+      fetch(k + A * T, rb, sb);
+      use(k, ra, sa);
+      fetch(k + 2 * A * T, ra, sa);
+      use(k + A * T, rb, sb);
     }
   } else {
     for (int64_t k = b + lane; k < e; k += T) {
@@ -127,28 +211,6 @@ __global__ void __launch_bounds__(kTileRows * T) k_apply_tile(const int32_t *__r
 
 // field values a tiled apply block may stage
 constexpr int kApplyCap = 2048;
-
-// A stencil record (four operators of one entry) as loaded, converted to
-// FP64 only where it is used: a conversion right after the load would wait
-// for it there.
-template <typename WT>
-struct WRec;
-template <>
-struct WRec<float> {
-  float4 v;
-  __device__ inline void load(const void *w, int64_t k) { v = reinterpret_cast<const float4 *>(w)[k]; }
-  __device__ inline double get(int s) const { return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w; }
-};
-template <>
-struct WRec<double> {
-  double2 a, b;
-  __device__ inline void load(const void *w, int64_t k) {
-    const double2 *p = reinterpret_cast<const double2 *>(w) + 2 * k;
-    a = p[0];
-    b = p[1];
-  }
-  __device__ inline double get(int s) const { return s == 0 ? a.x : s == 1 ? a.y : s == 2 ? b.x : b.y; }
-};
 
 // ubar_j = sum_{i : j in S_i, i != j} c_ij ybar_i - ybar_j sum_{k in S_j, k != j} c_jk,
 // the first sum gathered through the reverse-edge map (entry (i,j) sits at
@@ -230,20 +292,48 @@ gf_status launch_apply(gf_ctx *ctx, const gf_nbr *nbr, const void *w, unsigned m
   const int nu = launch_units(nbr, units);
   const IOT *uu = (const IOT *)u;
   IOT *oo = (IOT *)out;
+  unsigned done = 0;  // units that went with an earlier launch
   for (int q = 0; q < nu; ++q) {
-    if (only_unit >= 0 && q != only_unit) continue;
+    if ((only_unit >= 0 && q != only_unit) || ((done >> q) & 1u)) continue;
     const LaunchUnit &lu = units[q];
     const int T = team_override > 0 ? team_override : ctx->ateam[lu.model][lu.band];
     const int32_t *sched = nbr->grouped + lu.row0;
     const int64_t nrows = lu.nrows;
     ProfScope prof(ctx, lu.model == 0 ? "apply_3d" : "apply_film");
     if (lu.tiled) {
-      const int cap = std::min(lu.tile_max, tile_capacity(ctx, kApplyCap));
-      const dim3 tgrid(grid_for(lu.ntiles, 1)), tblock(kTileRows * std::min(T, 32));
-      const size_t lds = sizeof(double) * cap;
-#define GF_APPLY_TILE(TT)                                                                                           \
-  hipLaunchKernelGGL((k_apply_tile<TT, WT, IOT>), tgrid, tblock, lds, ctx->stream, sched, nrows, nbr->row_ptr,      \
-                     nbr->col, nbr->slot, nbr->tile_off, nbr->tile_u, lu.tile0, cap, w, mask, uu, oo, nbr->n)
+      ApplyTiles at;
+      at.grouped = nbr->grouped;
+      at.nranges = 1;
+      at.tile0[0] = lu.tile0;
+      at.ntiles[0] = lu.ntiles;
+      at.row0[0] = lu.row0;
+      at.nrows[0] = lu.nrows;
+      at.tile0[1] = at.ntiles[1] = at.row0[1] = at.nrows[1] = 0;
+      int64_t blocks = lu.ntiles;
+      int tmax = lu.tile_max;
+      // one launch for both models' tiles
+      for (int q2 = q + 1; q2 < nu && only_unit < 0; ++q2) {
+        const LaunchUnit &l2 = units[q2];
+        if (!l2.tiled || ctx->ateam[l2.model][l2.band] != T) continue;
+        at.nranges = 2;
+        at.tile0[1] = l2.tile0;
+        at.ntiles[1] = l2.ntiles;
+        at.row0[1] = l2.row0;
+        at.nrows[1] = l2.nrows;
+        blocks = (lu.ntiles + 7) / 8 * 8 + l2.ntiles;
+        tmax = std::max(tmax, l2.tile_max);
+        done |= 1u << q2;
+      }
+      at.cap = std::min(tmax, tile_capacity(ctx, kApplyCap));
+      const dim3 tgrid(grid_for(blocks, 1)), tblock(kTileRows * std::min(T, 32));
+      const size_t lds = sizeof(double) * at.cap;
+      const bool nt = sizeof(WT) == 4 && (double)nbr->nnz * 4 * sizeof(WT) > kApplyStream;
+#define GF_APPLY_TILE_NT(TT, NT)                                                                                       \
+  hipLaunchKernelGGL((k_apply_tile<TT, WT, IOT, NT>), tgrid, tblock, lds, ctx->stream, at, nbr->row_ptr, nbr->col,  \
+                     nbr->slot, nbr->tile_off, nbr->tile_u, w, mask, uu, oo, nbr->n)
+#define GF_APPLY_TILE(TT)                                                                                              \
+  if (nt && TT >= 8) GF_APPLY_TILE_NT(TT, (sizeof(WT) == 4 && TT >= 8));                                               \
+  else GF_APPLY_TILE_NT(TT, false)
       switch (std::min(T, 32)) {
         case 4: GF_APPLY_TILE(4); break;
         case 8: GF_APPLY_TILE(8); break;
@@ -251,6 +341,7 @@ gf_status launch_apply(gf_ctx *ctx, const gf_nbr *nbr, const void *w, unsigned m
         default: GF_APPLY_TILE(32); break;
       }
 #undef GF_APPLY_TILE
+#undef GF_APPLY_TILE_NT
       GF_LAUNCH_CHECK(ctx);
       continue;
     }
