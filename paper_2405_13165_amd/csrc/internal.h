@@ -115,13 +115,54 @@ struct gf_nbr {
   int64_t ntiles = 0;
   int64_t tile_start[3] = {0};  // host: tiles of model m are [tile_start[m], tile_start[m+1])
   int32_t tile_max[2] = {0};    // host: largest tile list of each model
+  int64_t tile_total = 0;       // host: length of tile_u
+  int64_t n_rows = 0;           // particles [n_rows, n) are ghosts: their rows hold only themselves
+  // Transposed tiles, built lazily where every row is tiled (max_row <=
+  // kTileBandRow): what the adjoints need to add up, per tile, the entries that
+  // refer to one neighbour, and, per particle, its places in the tile lists.
+  // A tile's slots, by falling number of entries, are taken in groups of 64; a
+  // tile's block of tperm holds, 64 values at a time, the groups' lengths (the
+  // most entries of a slot), each group's slots (kSlotNone past the last), and
+  // each group's entries, four steps at a time (a lane's four together): step k
+  // holds the k-th entry of every slot in row order, or the number of entries
+  // of the tile where the slot has fewer.  Entries are counted row by row in
+  // tile order.
+  int64_t *tperm_off = nullptr;  // [ntiles + 1] first of each tile's block, in units of 64
+  uint16_t *tperm = nullptr;     // [64 tperm_off[ntiles]]
+  uint16_t *tself = nullptr;     // [kTileRows ntiles] slot of each team's own particle
+  int32_t *gptr = nullptr;      // [n + 1] places of each particle in tile_u ...
+  int32_t *gidx = nullptr;      // [tile_total] ... ascending
 };
 constexpr int kTileRows = 32;
+constexpr int kSlotNone = 0xffff;
 constexpr int kTileBand = 2;                   // bands 0..kTileBand are tiled
 constexpr int kTileBandRow = 128;              // = kBandHi[kTileBand]
 // entries of padding after the slot array (and the solver's matrix values),
 // so that the SpMV can read a row's entries in aligned groups of four
 constexpr int kQuadPad = 4;
+
+// where the tiles' rows lie in the grouped order
+struct TileRows {
+  const int32_t *grouped;
+  int64_t tile_start[3];
+  int64_t row0[2], nrows[2];
+};
+inline TileRows tile_rows(const gf_nbr *nb) {
+  TileRows tr;
+  tr.grouped = nb->grouped;
+  for (int k = 0; k < 3; ++k) tr.tile_start[k] = nb->tile_start[k];
+  for (int m = 0; m < 2; ++m) {
+    tr.row0[m] = nb->group_start[m * GF_NBAND];
+    tr.nrows[m] = nb->group_start[m * GF_NBAND + kTileBand + 1] - tr.row0[m];
+  }
+  return tr;
+}
+// row `team` of tile t, -1 past the model's last
+__host__ __device__ inline int32_t tile_row(const TileRows &tr, int64_t t, int team) {
+  const int m = (t >= tr.tile_start[1]) ? 1 : 0;
+  const int64_t r = (t - tr.tile_start[m]) * kTileRows + team;
+  return r < tr.nrows[m] ? tr.grouped[tr.row0[m] + r] : -1;
+}
 
 // Launch units of the batched kernels: per model, the tiled rows (bands
 // 0..kTileBand) and each untiled band.  Team sizes live in
@@ -226,6 +267,9 @@ gf_status check_nbr(gf_ctx *ctx, const gf_nbr *nbr, int64_t n);
 gf_status ensure_rev(gf_ctx *ctx, gf_nbr *nbr);
 // grouped row offsets, positions and twin map (needs the reverse-edge map)
 gf_status ensure_grouped_rows(gf_ctx *ctx, gf_nbr *nbr);
+// the transposed tiles; only for handles whose rows are all tiled
+inline bool all_tiled(const gf_nbr *nbr) { return nbr->ntiles > 0 && nbr->max_row <= kTileBandRow; }
+gf_status ensure_tile_transpose(gf_ctx *ctx, gf_nbr *nbr);
 gf_status tune_apply(gf_ctx *ctx, const gf_nbr *nbr, const void *w, gf_dtype wtype);
 
 // device-wide exclusive scans (in place allowed): out[k] = sum_{t<k} in[t],

@@ -1422,6 +1422,184 @@ gf_status ensure_grouped_rows(gf_ctx *ctx, gf_nbr *nbr) {
 }
 
 namespace {
+// Room for each transposed tile, in units of 64: the lengths, ceil(U / 64)
+// groups of slots and at most kTileRows + entries / 64 steps (a group's length is
+// at most the fewest entries of a slot of the group before, so that the padding
+// of all groups together is less than the first group), rounded up to fours per
+// group.
+__global__ void __launch_bounds__(kBlock) k_tile_room(TileRows tr, const int64_t *__restrict__ row_ptr,
+                                                      const int64_t *__restrict__ tile_off, int64_t nt,
+                                                      int32_t *__restrict__ room) {
+  const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t t = gt / kTileRows;
+  if (t >= nt) return;  // (teams of kTileRows lanes leave together)
+  const int32_t i = tile_row(tr, t, (int)(gt % kTileRows));
+  int len = i >= 0 ? (int)(row_ptr[i + 1] - row_ptr[i]) : 0;
+#pragma unroll
+  for (int o = kTileRows / 2; o > 0; o >>= 1) len += __shfl_xor(len, o, kTileRows);
+  if (gt % kTileRows == 0) room[t] = 1 + 4 * ((int)(tile_off[t + 1] - tile_off[t] + 63) / 64) + kTileRows + len / 64;
+}
+
+// A block per tile, a team of 8 lanes per row.  s_mask: the rows that list each
+// slot, a bit each (a row lists a slot at most once), so an entry's place among
+// its slot's is the number of lower bits: no pass waits for another row.  The
+// slots' order among those of equal length is whichever comes first: it moves
+// no sum's terms.  The block is put together in LDS and written in order.
+__global__ void __launch_bounds__(kBlock) k_tile_transpose(TileRows tr, const int64_t *__restrict__ row_ptr,
+                                                           const int32_t *__restrict__ col,
+                                                           const uint16_t *__restrict__ slot,
+                                                           const int64_t *__restrict__ tile_off,
+                                                           const int64_t *__restrict__ tperm_off, int cap,
+                                                           uint16_t *__restrict__ tperm, uint16_t *__restrict__ tself) {
+  constexpr int T = kBlock / kTileRows, Q = kTileBandRow / T;
+  extern __shared__ uint32_t s_mask[];                          // [cap]
+  uint16_t *s_pos = reinterpret_cast<uint16_t *>(s_mask + cap);  // [cap] place in the order
+  uint16_t *s_out = s_pos + ((cap + 1) & ~1);                    // the block
+  __shared__ int s_off[kTileRows + 1];
+  __shared__ int s_bin[kTileRows + 1];  // slots of each length, then the next place of each
+  __shared__ int s_first[64];           // first step of each group
+  const int64_t t = blockIdx.x;
+  const int U = (int)(tile_off[t + 1] - tile_off[t]), G = (U + 63) / 64;
+  const int team = threadIdx.x / T, lane = threadIdx.x % T;
+  const int32_t i = tile_row(tr, t, team);
+  const int64_t b = i >= 0 ? row_ptr[i] : 0;
+  const int n = i >= 0 ? (int)(row_ptr[i + 1] - b) : 0;
+  for (int s = threadIdx.x; s < U; s += kBlock) s_mask[s] = 0;
+  if (threadIdx.x <= kTileRows) s_bin[threadIdx.x] = 0;
+  if (threadIdx.x < 64) s_out[threadIdx.x] = 0;
+  if (threadIdx.x == 0) s_off[0] = 0;
+  if (lane == 0) s_off[team + 1] = n;
+  __syncthreads();
+  // (the row's slots stay in registers; past its end the last one, unused)
+  uint16_t sl[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (n > q * T) sl[q] = slot[b + min(lane + q * T, n - 1)];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (lane + q * T < n) atomicOr(&s_mask[sl[q]], 1u << team);
+  if (threadIdx.x < 64) {
+    int v = threadIdx.x < kTileRows ? s_off[threadIdx.x + 1] : 0;
+    v = wave_scan_add(v);
+    if (threadIdx.x < kTileRows) s_off[threadIdx.x + 1] = v;
+  }
+  __syncthreads();
+  for (int s = threadIdx.x; s < U; s += kBlock) atomicAdd(&s_bin[__popc(s_mask[s])], 1);
+  __syncthreads();
+  if (threadIdx.x < 64) {  // lane l: length kTileRows - l
+    const int v = threadIdx.x <= kTileRows ? s_bin[kTileRows - threadIdx.x] : 0;
+    const int inc = wave_scan_add(v);
+    if (threadIdx.x <= kTileRows) s_bin[kTileRows - threadIdx.x] = inc - v;
+  }
+  for (int s = U + threadIdx.x; s < 64 * G; s += kBlock) s_out[64 + s] = kSlotNone;
+  __syncthreads();
+  for (int s = threadIdx.x; s < U; s += kBlock) {
+    const int len = __popc(s_mask[s]), p = atomicAdd(&s_bin[len], 1);
+    s_pos[s] = (uint16_t)p;
+    s_out[64 + p] = (uint16_t)s;
+    if (p % 64 == 0) s_out[p / 64] = (uint16_t)len;
+  }
+  __syncthreads();
+  const int E = s_off[kTileRows];
+  uint16_t *steps = s_out + 64 * (1 + G);
+  if (threadIdx.x < 64) {
+    const int v = (s_out[threadIdx.x] + 3) & ~3, inc = wave_scan_add(v);
+    s_first[threadIdx.x] = inc - v;
+    if (threadIdx.x == 63) s_bin[0] = inc;
+  }
+  __syncthreads();
+  const int S = s_bin[0];
+  for (int k = threadIdx.x; k < 64 * S; k += kBlock) steps[k] = (uint16_t)E;
+  __syncthreads();
+  const int e0 = s_off[team];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (lane + q * T < n) {
+      const int s = sl[q], p = s_pos[s], lower = __popc(s_mask[s] & ((1u << team) - 1));
+      steps[64 * (s_first[p / 64] + (lower & ~3)) + 4 * (p % 64) + (lower & 3)] = (uint16_t)(e0 + lane + q * T);
+      if (col[b + lane + q * T] == i) tself[kTileRows * t + team] = (uint16_t)s;
+    }
+  __syncthreads();
+  uint32_t *out = reinterpret_cast<uint32_t *>(tperm + 64 * tperm_off[t]);
+  for (int k = threadIdx.x; k < 32 * (1 + G + S); k += kBlock) out[k] = reinterpret_cast<const uint32_t *>(s_out)[k];
+}
+
+// places of each particle, and the order in which they came (whatever it was)
+__global__ void __launch_bounds__(kBlock) k_places_count(const int32_t *__restrict__ tile_u, int64_t total,
+                                                         int32_t *__restrict__ cnt, int32_t *__restrict__ rank) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < total) rank[k] = atomicAdd(&cnt[tile_u[k]], 1);
+}
+__global__ void __launch_bounds__(kBlock) k_places_fill(const int32_t *__restrict__ tile_u, int64_t total,
+                                                        const int32_t *__restrict__ gptr,
+                                                        const int32_t *__restrict__ rank, int32_t *__restrict__ raw) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < total) raw[gptr[tile_u[k]] + rank[k]] = (int32_t)k;
+}
+// each particle's places ascending (a few tens): a place goes after the smaller ones
+__global__ void __launch_bounds__(kBlock) k_places_sort(const int32_t *__restrict__ gptr, int64_t n,
+                                                        const int32_t *__restrict__ raw, int32_t *__restrict__ gidx) {
+  constexpr int T = 16;
+  const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t j = gt / T;
+  if (j >= n) return;
+  const int32_t a = gptr[j], b = gptr[j + 1];
+  for (int32_t k = a + (int)(gt % T); k < b; k += T) {
+    const int32_t v = raw[k];
+    int32_t r = a;
+#pragma unroll 4
+    for (int32_t q = a; q < b; ++q) r += raw[q] < v ? 1 : 0;
+    gidx[r] = v;
+  }
+}
+}  // namespace
+
+gf_status ensure_tile_transpose(gf_ctx *ctx, gf_nbr *nb) {
+  if (nb->gidx) return GF_OK;
+  if (nb->nnz > (int64_t)0x7fffffff)
+    return set_error(ctx, GF_ECAPACITY, "the adjoints' maps hold 32-bit positions; %lld entries exceed them",
+                     (long long)nb->nnz);
+  const int64_t nt = nb->ntiles, n = nb->n, total = nb->tile_total;
+  int32_t *gidx = nullptr;  // set in the handle last: it says that everything is there
+  const int64_t room = nb->nnz / 64 + 4 * (total / 64 + nt) + nt * (kTileRows + 1) + 4;  // see k_tile_room
+  if ((!nb->tperm_off && !take(nb, nb->tperm_off, nt + 1)) || (!nb->tperm && !take(nb, nb->tperm, 64 * room)) ||
+      (!nb->tself && !take(nb, nb->tself, kTileRows * nt)) || (!nb->gptr && !take(nb, nb->gptr, n + 1)) ||
+      !take(nb, gidx, total))
+    return set_error(ctx, GF_ENOMEM, "transposed tile allocation failed");
+  Arena ar;
+  gf_status st;
+  const int64_t nc = std::max(n, nt);
+  if ((st = ensure_scratch(ctx, arena_bytes({sizeof(int32_t) * nc, sizeof(int64_t) * scan_tmp_elems(nc + 1),
+                                             sizeof(int32_t) * total, sizeof(int32_t) * total}), &ar)))
+    return st;
+  int32_t *cnt = ar.take<int32_t>(nc);
+  int64_t *tmp = ar.take<int64_t>(scan_tmp_elems(nc + 1));
+  int32_t *rank = ar.take<int32_t>(total), *raw = ar.take<int32_t>(total);
+  hipStream_t sm = ctx->stream;
+  ProfScope prof(ctx, "tile_transpose");
+  const TileRows tr = tile_rows(nb);
+  hipLaunchKernelGGL(k_tile_room, dim3(grid_for(nt * kTileRows, kBlock)), dim3(kBlock), 0, sm, tr, nb->row_ptr,
+                     nb->tile_off, nt, cnt);
+  GF_LAUNCH_CHECK(ctx);
+  if ((st = scan_i32_to_i64(ctx, cnt, nb->tperm_off, nt, tmp))) return st;
+  const int cap = std::max(nb->tile_max[0], nb->tile_max[1]);
+  const size_t lds = sizeof(uint32_t) * cap + sizeof(uint16_t) * ((cap + 1) & ~1) +
+                     sizeof(uint16_t) * 64 * (1 + 4 * ((cap + 63) / 64) + kTileRows + kTileRows * (size_t)nb->max_row / 64);
+  hipLaunchKernelGGL(k_tile_transpose, dim3((unsigned)nt), dim3(kBlock), lds, sm, tr, nb->row_ptr, nb->col, nb->slot,
+                     nb->tile_off, nb->tperm_off, cap, nb->tperm, nb->tself);
+  hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, cnt, n, 0);
+  hipLaunchKernelGGL(k_places_count, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, cnt, rank);
+  GF_LAUNCH_CHECK(ctx);
+  if ((st = scan_i32_to_i32(ctx, cnt, nb->gptr, n, (int32_t *)tmp))) return st;
+  hipLaunchKernelGGL(k_places_fill, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, nb->gptr, rank,
+                     raw);
+  hipLaunchKernelGGL(k_places_sort, dim3(grid_for(n * 16, kBlock)), dim3(kBlock), 0, sm, nb->gptr, n, raw, gidx);
+  GF_LAUNCH_CHECK(ctx);
+  nb->gidx = gidx;
+  return GF_OK;
+}
+
+namespace {
 
 // Cut the tiled groups into tiles and build slot[], tile_u[], tile_off[].
 gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
@@ -1469,6 +1647,7 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   GF_HIP(ctx, hipStreamSynchronize(sm));
   for (int q = 0; q < tg.nq; ++q) nb->tile_max[tg.gsel[q]] = (int32_t)hp[q];  // per model
   const int64_t total = hp[2];
+  nb->tile_total = total;
   if (!take(nb, nb->tile_u, total))
     return set_error(ctx, GF_ENOMEM, "neighbour tile list allocation failed");
   ProfScope prof(ctx, "nbr_tile_compact");
@@ -1637,6 +1816,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   nb->pool = ctx->pool;
   nb->device = ctx->device;
   nb->n = n;
+  nb->n_rows = n_rows;
   nb->cross = cross_model ? 1 : 0;
   auto fail = [&](gf_status s2) { free_nbr(nb); return s2; };
   if (!take(nb, nb->row_ptr, n + 1) || !take(nb, nb->grouped, n))

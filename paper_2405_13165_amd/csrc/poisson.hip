@@ -194,27 +194,14 @@ struct PackedTiles {
 };
 constexpr int kGroups = kTileRows / 8;
 
-// where the tiles' rows lie in the grouped order
-struct TileRows {
-  const int32_t *grouped;
-  int64_t tile_start[3];
-  int64_t row0[2], nrows[2];
-};
-
 // a wave per tile: rows by falling length (ties by place), group lengths
 __global__ void __launch_bounds__(kBlock) k_pack_rows(TileRows tr, const int64_t *__restrict__ row_ptr,
                                                       int32_t *__restrict__ prow, int32_t *__restrict__ gq) {
   const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (t >= tr.tile_start[2]) return;
-  const int m = (t >= tr.tile_start[1]) ? 1 : 0;
-  const int64_t r = (t - tr.tile_start[m]) * kTileRows + lane;
-  int32_t i = -1;
-  int len = 0;
-  if (lane < kTileRows && r < tr.nrows[m]) {
-    i = tr.grouped[tr.row0[m] + r];
-    len = (int)(row_ptr[i + 1] - row_ptr[i]);
-  }
+  const int32_t i = lane < kTileRows ? tile_row(tr, t, lane) : -1;
+  const int len = i >= 0 ? (int)(row_ptr[i + 1] - row_ptr[i]) : 0;
   int rank = 0;
 #pragma unroll
   for (int o = 0; o < kTileRows; ++o) {
@@ -1138,13 +1125,7 @@ extern "C" gf_status gf_poisson_solve(gf_ctx *ctx, const gf_particles *p, const 
   sv.tl.pk.goff = goff; sv.tl.pk.prow = prow; sv.tl.pk.slot = pslot;
   const AsmArgs ga = asm_args(p, nbr, w64, row_type, prm.zeta, prm.implicit_a, GF_ROW_IMPLICIT, dinv64, dinv32, bad);
   if (sv.tiled) {
-    TileRows tr;
-    tr.grouped = nbr->grouped;
-    for (int k = 0; k < 3; ++k) tr.tile_start[k] = nbr->tile_start[k];
-    for (int m = 0; m < 2; ++m) {
-      tr.row0[m] = nbr->group_start[m * GF_NBAND];
-      tr.nrows[m] = nbr->group_start[m * GF_NBAND + kTileBand + 1] - tr.row0[m];
-    }
+    const TileRows tr = tile_rows(nbr);
     hipLaunchKernelGGL(k_pack_rows, dim3(grid_for(nbr->ntiles, kBlock / 64)), dim3(kBlock), 0, sm, tr, nbr->row_ptr, prow, gq);
     GF_LAUNCH_CHECK(ctx);
     if ((st = scan_i32_to_i64(ctx, gq, goff, ngroups, gtmp))) return st;

@@ -1,0 +1,81 @@
+"""The adjoints over transposed tiles where they can go wrong: one partial tile, tiles whose lists fill few or many groups of
+64, rows from a few to 128 entries, equal and unequal supports, and rows beyond the tiles (the general path)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2405_13165_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def cloud(kind, size):
+    rng = np.random.default_rng([47, size])
+    if kind == "film":
+        i, j = (a.ravel() for a in np.meshgrid(np.arange(size), np.arange(7), indexing="ij"))
+        x, y = i + rng.uniform(-0.2, 0.2, i.size), j + rng.uniform(-0.2, 0.2, i.size)
+        z = np.zeros(i.size)
+        return W._pack(x, y, z, np.full(i.size, 3.0), np.ones(i.size), np.full(i.size, W.WALL), z, z, z + 1)
+    x, y, z = W.jittered_cube(size, 1.0, rng)
+    n = x.size
+    h = np.full(n, 2.6)
+    if kind == "unequal":  # rows of at most 128 entries, supports that differ within a tile
+        h = rng.uniform(2.5, 2.75, n)
+    if kind == "uneven":   # rows of more than 128 entries
+        h = np.where(x < size / 2, 2.6, 3.9)
+    return W._pack(x, y, z, h, np.zeros(n), np.zeros(n))
+
+
+@pytest.mark.parametrize("mask", [0x1, 0x8, 0x7, 0xF])
+@pytest.mark.parametrize("kind,size", [("film", 5), ("film", 41), ("cube", 3), ("cube", 4), ("cube", 13), ("unequal", 12),
+                                       ("uneven", 12)])
+def test_adjoints(kind, size, mask):
+    """Against the oracle: the application's adjoint to 1e-12 of its largest value (sums of at most a few hundred FP64
+    terms), the position adjoint to 1e-9 (times the stencils' condition, up to 1e6 rounding errors)."""
+    from paper_2405_13165_amd import gfdm as g
+    d = cloud(kind, size)
+    ctx = g.Context(0)
+    p = g.Particles.from_dict(ctx, d)
+    nb = g.build_neighbours(ctx, p)
+    assert (nb.max_row > 128) == (kind == "uneven")
+    rp, col = (t.cpu().numpy() for t in nb.export())
+    rng = np.random.default_rng([size, mask])
+    K = bin(mask).count("1")
+    yb = rng.standard_normal((K, p.n))
+    ybt = torch.as_tensor(yb, device=ctx.device)
+    for dt in (g.GF_F64, g.GF_F32):
+        w = g.gfdm_weights(ctx, p, nb, g.GF_BATCHED, dt)
+        ub = g.apply_stencil_adjoint(ctx, nb, w, ybt, op_mask=mask).cpu().numpy()
+        ub_o = oracle.apply_adjoint(rp, col, w.cpu().numpy().astype(np.float64), yb, op_mask=mask)
+        assert np.abs(ub - ub_o).max() <= 1e-12 * np.abs(ub_o).max()
+    u = np.sin(0.3 * d["x"]) * np.cos(0.2 * d["y"]) + 0.1 * d["z"]
+    xb_o = oracle.weights_adjoint_x(d, rp, col, u, yb, op_mask=mask)
+    ut = torch.as_tensor(u, device=ctx.device)
+    xb = g.gfdm_weights_adjoint(ctx, p, nb, ut, ybt, op_mask=mask)
+    assert np.abs(xb.cpu().numpy() - xb_o).max() <= 1e-9 * np.abs(xb_o).max()
+    assert torch.equal(xb, g.gfdm_weights_adjoint(ctx, p, nb, ut, ybt, op_mask=mask))  # the order of every sum is fixed
+
+
+def test_apply_rows_at_every_offset():
+    """The tiled application's aligned blocks: rows that begin at every offset of a block (sums of at most 128 FP64 terms of
+    FP64 and FP32 stencils, so 1e-12 of the largest value; 2e-6 with FP32 output)."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx = g.Context(0)
+    for kind, size in (("film", 23), ("cube", 3), ("cube", 12), ("unequal", 9)):
+        d = cloud(kind, size)
+        p = g.Particles.from_dict(ctx, d)
+        nb = g.build_neighbours(ctx, p)
+        rp, col = (t.cpu().numpy() for t in nb.export())
+        assert len(set(rp[:-1] % 16)) == 16 or p.n < 40
+        u = np.random.default_rng(size).standard_normal(p.n)
+        for dt in (g.GF_F64, g.GF_F32):
+            w = g.gfdm_weights(ctx, p, nb, g.GF_BATCHED, dt)
+            w64 = w.cpu().numpy().astype(np.float64)
+            for mask in (0x8, 0xF):
+                ref = oracle.apply(rp, col, w64, u, op_mask=mask)
+                y = g.apply_stencil(ctx, nb, w, torch.as_tensor(u, device=ctx.device), op_mask=mask).cpu().numpy()
+                assert np.abs(y - ref).max() <= 1e-12 * np.abs(ref).max()
+                y = g.apply_stencil(ctx, nb, w, torch.as_tensor(u, device=ctx.device).float(), op_mask=mask)
+                ref = oracle.apply(rp, col, w64, u.astype(np.float32).astype(np.float64), op_mask=mask)
+                assert np.abs(y.cpu().numpy() - ref).max() <= 2e-6 * np.abs(ref).max()
