@@ -102,7 +102,7 @@ __device__ inline double support_weight_raw(double d2, double cs, const WeightFn
     const float e = __builtin_amdgcn_exp2f((float)fma(d2, cs, -k));
     return ldexp((double)e, (int)k) - wf.ea;
   } else {
-    return exp2(d2 * cs) - wf.ea;
+    return exp2_raw(d2 * cs) - wf.ea;
   }
 }
 // the same with q^2 = d2 / r^2
