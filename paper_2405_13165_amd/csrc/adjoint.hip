@@ -442,27 +442,18 @@ k_adjoint_tile(AArgs a, ATile at, int cap) {
   const uint32_t line = TileSum<kBlock>::warm(block, at.tperm_off[t + 1] - at.tperm_off[t]);
   const double h0 = a.h[at.tile_u[u0]];  // (a tile lists at least its own rows)
   bool same = true;
-  // (every index, then every value of a round is requested before the first is used)
-  for (int s0 = threadIdx.x; s0 < U; s0 += 4 * kBlock) {
-    int32_t j[4];
-    double v[4][5];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) j[q] = at.tile_u[u0 + min(s0 + q * kBlock, U - 1)];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      v[q][0] = a.x[j[q]]; v[q][1] = a.y[j[q]]; v[q][2] = a.z[j[q]]; v[q][3] = a.u[j[q]]; v[q][4] = a.h[j[q]];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int s = s0 + q * kBlock;
-      if (s < U) {
+  double v[kStage][5];
+  stage_tile<kBlock>(
+      at.tile_u + u0, U,
+      [&](int q, int32_t j) {
+        v[q][0] = a.x[j]; v[q][1] = a.y[j]; v[q][2] = a.z[j]; v[q][3] = a.u[j]; v[q][4] = a.h[j];
+      },
+      [&](int q, int s) {
         sxy[s] = make_double2(v[q][0], v[q][1]);
         szu[s] = make_double2(v[q][2], v[q][3]);
         sh[s] = v[q][4];
-      }
-      same = same && v[q][4] == h0;
-    }
-  }
+        same = same && v[q][4] == h0;
+      });
   if (lane == 0) s_len[team] = n;
   if constexpr (M == 6) tangent_frame(nrm[0], nrm[1], nrm[2], g.t1, g.t2);
   bool on = n >= M && status < 2;  // the same on every lane of the team

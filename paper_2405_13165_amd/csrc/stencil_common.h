@@ -492,6 +492,29 @@ __device__ inline double team_max(double v, int width) {
   return v;
 }
 
+// Stage a tile's list: load(q, j) requests what neighbour j needs into the
+// caller's registers of step q, store(q, s) puts it at place s.  Every index of
+// kStage steps of the block is requested before the first neighbour's values, and
+// those before the first is used: two latencies per kStage steps instead of two
+// per step, which a block waits for with nothing else to do.
+constexpr int kStage = 4;
+template <int NT, class Load, class Store>
+__device__ inline void stage_tile(const int32_t *__restrict__ list, int cnt, Load &&load, Store &&store) {
+#pragma unroll 1
+  for (int s0 = 0; s0 < cnt; s0 += kStage * NT) {
+    int32_t j[kStage];
+#pragma unroll
+    for (int q = 0; q < kStage; ++q)
+      if (s0 + q * NT < cnt) j[q] = list[min(s0 + q * NT + (int)threadIdx.x, cnt - 1)];
+#pragma unroll
+    for (int q = 0; q < kStage; ++q)
+      if (s0 + q * NT < cnt) load(q, j[q]);
+#pragma unroll
+    for (int q = 0; q < kStage; ++q)
+      if (s0 + q * NT + (int)threadIdx.x < cnt) store(q, s0 + q * NT + (int)threadIdx.x);
+  }
+}
+
 // A block of NT threads adds up a tile's terms s_t[entry] per slot, out[C slot] =
 // the sum of a slot's terms in row order, through the tile's block p of the
 // transposed tiles (U slots); s_t[entries of the tile] is zero.  A wave takes a

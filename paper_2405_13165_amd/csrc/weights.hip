@@ -714,14 +714,19 @@ k_weights_tile(WArgs a, TileArgs ta, const uint16_t *__restrict__ slot) {
   int same = 1;
   if (staged) {
     const double h0 = a.h[ta.u[u0]];
-    for (int s = threadIdx.x; s < cnt; s += blockDim.x) {
-      const int32_t j = ta.u[u0 + s];
-      const double hj = a.h[j];
-      s_xy[s] = make_double2(a.x[j], a.y[j]);
-      s_zh[s] = make_double2(a.z[j], hj);
-      same &= hj == h0;
-      if constexpr (FUSED) s_u[s] = a.u[j];
-    }
+    double v[kStage][5];
+    stage_tile<kTileRows * T>(
+        ta.u + u0, cnt,
+        [&](int q, int32_t j) {
+          v[q][0] = a.x[j]; v[q][1] = a.y[j]; v[q][2] = a.z[j]; v[q][3] = a.h[j];
+          if constexpr (FUSED) v[q][4] = a.u[j];
+        },
+        [&](int q, int s) {
+          s_xy[s] = make_double2(v[q][0], v[q][1]);
+          s_zh[s] = make_double2(v[q][2], v[q][3]);
+          same &= v[q][3] == h0;
+          if constexpr (FUSED) s_u[s] = v[q][4];
+        });
   }
   // block-wide AND of `same`: a ballot per wave, one flag per wave, one barrier
   // (which also publishes the staged tile)
