@@ -11,7 +11,7 @@
 // to the particle itself keep an exactly planar neighbourhood exactly planar
 // (its third eigenvalue is exactly zero), and with |d| <= h the subtraction
 // loses no more than a few ulp of the largest eigenvalue.  The neighbour
-// kinds are counted in 16-bit fields of one integer.  The team writes the
+// kinds are counted in fields of one integer.  The team writes the
 // covariance and the counts of its row (one 64-byte record), and a second
 // kernel runs the eigen solve and the classification with one particle per
 // lane: inside the team kernel only one lane of each team would do that
@@ -146,8 +146,8 @@ __device__ void pca_finish(const PcaArgs &a, int32_t i, int n_int, int n_fs, dou
   a.raw[i] = f;
 }
 
-// A neighbour as (x, y, z, 16 * kind code), the code being the kind 0..2 or 3
-// for anything else: the shift that counts it in its 16-bit field.
+// 16 * kind code, the code being the kind 0..2 or 3 for anything else: the
+// shift that counts it in its 16-bit field (8 * code in the tiles' 8-bit fields).
 __device__ inline double pca_code_of(int k) { return (double)(16 * ((k >= 0 && k <= 2) ? k : 3)); }
 // The tile's neighbours in LDS as (x, y) 16-byte records, z and the kind
 // code in arrays of their own: 25 bytes per neighbour instead of a 32-byte
@@ -158,15 +158,14 @@ struct PcaRec {
   const double2 *xy;
   const double *zz;
   const uint8_t *cc;
-  __device__ double4 operator[](int s) const {
+  __device__ double3 operator[](int s) const {
     const double2 p = xy[s];
-    return make_double4(p.x, p.y, zz[s], (double)cc[s]);
+    return make_double3(p.x, p.y, zz[s]);
   }
 };
 struct PcaTile {   // staged in LDS, addressed by slot[]
   static constexpr bool kQuads = true;
   PcaRec sp;
-  const uint16_t *slot;
 };
 struct PcaGlobal {  // gathered from global memory
   static constexpr bool kQuads = false;
@@ -176,43 +175,66 @@ struct PcaGlobal {  // gathered from global memory
 // 128 neighbours): each lane keeps four entries in flight
 constexpr int kTeamWide = 16;
 
+// What a tiled row reads besides the tile, requested before the staging: its
+// extent, position and slots, the aligned quads q0 + lane, q0 + lane + T, ...
+// (q0 the row's first)
+template <int T>
+struct PcaPre {
+  static constexpr int kPq = 128 / (4 * T) + 1;  // quads per lane for rows of at most 128 entries
+  int64_t b, e;
+  double x, y, z;
+  ushort4 ss[kPq];
+  __device__ void load(const PcaArgs &a, const uint16_t *slot, int32_t i, int lane) {
+    b = a.row_ptr[i];
+    e = a.row_ptr[i + 1];
+    x = a.x[i]; y = a.y[i]; z = a.z[i];
+    const int64_t q0 = (b >> 2) + lane;
+#pragma unroll
+    for (int j = 0; j < kPq; ++j) {
+      const int64_t k = 4 * (q0 + j * T);
+      if (k < e) ss[j] = *reinterpret_cast<const ushort4 *>(slot + k);
+    }
+  }
+};
+
 template <int T, class F>
-__device__ void pca_row(const PcaArgs &a, int32_t i, int lane, const F &fetch) {
-  const int64_t b = a.row_ptr[i], e = a.row_ptr[i + 1];
-  const double xi = a.x[i], yi = a.y[i], zi = a.z[i];
+__device__ void pca_row(const PcaArgs &a, int32_t i, int lane, const F &fetch, const PcaPre<T> *pre = nullptr) {
+  const int64_t b = F::kQuads ? pre->b : a.row_ptr[i], e = F::kQuads ? pre->e : a.row_ptr[i + 1];
+  const double xi = F::kQuads ? pre->x : a.x[i], yi = F::kQuads ? pre->y : a.y[i], zi = F::kQuads ? pre->z : a.z[i];
   const bool need_kinds = a.raw && a.kind;
   double c[6];
   int n_int = 0, n_fs = 0;
   uint64_t kinds = 0;
   double mx = 0.0, my = 0.0, mz = 0.0;
   double sxx = 0.0, sxy = 0.0, sxz = 0.0, syy = 0.0, syz = 0.0, szz = 0.0;
-  auto visit = [&](const double4 &pj) {
-    const double dx = pj.x - xi, dy = pj.y - yi, dz = pj.z - zi;
-    mx += dx; my += dy; mz += dz;
-    sxx += dx * dx; sxy += dx * dy; sxz += dx * dz;
-    syy += dy * dy; syz += dy * dz; szz += dz * dz;
-    if (need_kinds) kinds += (uint64_t)1 << (int)pj.w;
-  };
   if constexpr (F::kQuads) {
-    // entries 4q .. 4q+3 of the aligned quads q0 + lane, q0 + lane + T, ...; a quad may reach
-    // up to three entries into the neighbouring rows (padded slot array): those are skipped
-    constexpr int kPq = 128 / (4 * T) + 1;  // quads per lane for rows of at most 128 entries
-    const int64_t q0 = (b >> 2) + lane;
-    ushort4 ss[kPq];
+    // a quad may reach up to three entries into the neighbouring rows (padded slot array): those are skipped.
+    // A tiled row has at most 128 entries, so its kinds are counted in 8-bit fields.
+    const unsigned n = (unsigned)(e - b);
+    uint32_t k8 = 0;
+    auto visit = [&](int s) {
+      const double3 pj = fetch.sp[s];
+      const double dx = pj.x - xi, dy = pj.y - yi, dz = pj.z - zi;
+      mx += dx; my += dy; mz += dz;
+      sxx += dx * dx; sxy += dx * dy; sxz += dx * dz;
+      syy += dy * dy; syz += dy * dz; szz += dz * dz;
+      k8 += 1u << fetch.sp.cc[s];
+    };
 #pragma unroll
-    for (int j = 0; j < kPq; ++j) {
-      const int64_t k = 4 * (q0 + j * T);
-      if (k < e) ss[j] = *reinterpret_cast<const ushort4 *>(fetch.slot + k);
-    }
-#pragma unroll
-    for (int j = 0; j < kPq; ++j) {
-      const int64_t k = 4 * (q0 + j * T);
-      if (k < e) {
-        if (k >= b) visit(fetch.sp[ss[j].x]);
-        if (k + 1 >= b && k + 1 < e) visit(fetch.sp[ss[j].y]);
-        if (k + 2 >= b && k + 2 < e) visit(fetch.sp[ss[j].z]);
-        if (k + 3 < e) visit(fetch.sp[ss[j].w]);
+    for (int j = 0; j < PcaPre<T>::kPq; ++j) {
+      const int k = 4 * (lane + j * T) - (int)(b & 3);  // place in the row of the quad's first entry
+      if (k < (int)n) {
+        const ushort4 ss = pre->ss[j];
+        if ((unsigned)k < n) visit(ss.x);
+        if ((unsigned)(k + 1) < n) visit(ss.y);
+        if ((unsigned)(k + 2) < n) visit(ss.z);
+        if ((unsigned)(k + 3) < n) visit(ss.w);
       }
+    }
+    if (need_kinds) {
+      k8 = (uint32_t)team_sum((int)k8, T);
+      kinds = (uint64_t)(k8 & 0xff) | (uint64_t)(k8 >> 8 & 0xff) << 16 | (uint64_t)(k8 >> 16 & 0xff) << 32 |
+              (uint64_t)(k8 >> 24) << 48;
     }
   } else {
     // entries k0, k0 + T, k0 + 2T, k0 + 3T per step, every load of a step issued before the first
@@ -245,7 +267,7 @@ __device__ void pca_row(const PcaArgs &a, int32_t i, int lane, const F &fetch) {
   my = team_sum(my, T);
   mz = team_sum(mz, T);
   if (need_kinds) {
-    kinds = team_sum(kinds, T);
+    if constexpr (!F::kQuads) kinds = team_sum(kinds, T);
     // i is in S_i once: remove its own kind
     const int ko = (int)a.kind[i];
     kinds -= (uint64_t)1 << (16 * ((ko >= 0 && ko <= 2) ? ko : 3));
@@ -276,33 +298,54 @@ __global__ void __launch_bounds__(kBlock) k_pca_finish(PcaArgs a, int64_t n) {
   pca_finish(a, (int32_t)i, (int)(uint32_t)cnt, (int)(uint32_t)(cnt >> 32), r0.x, r0.y, r1.x, r1.y, r2.x, r2.y);
 }
 
-// tiled rows: one neighbour tile per block, kTileRows teams
-__global__ void __launch_bounds__(kTileRows * kTeam) k_pca_tile(PcaArgs a, const int64_t *__restrict__ toff,
+// Tiled rows: one neighbour tile per block, kTileRows teams, both models in one
+// launch (a block per tile of either; the film's short rows fill the chip while
+// the last 3D tiles finish).
+//
+// What bounds it: latency and LDS (0.2 GB of lists and records on the mixed
+// cloud would take 35 us, its vector instructions 31).  The row's extent,
+// position and slots are requested before the tile's list, so that a block waits
+// for three reads in a row instead of seven; 58 us against 67 in two launches.
+// Teams of 8 take 83 us (twice the sums over lanes), more waves by spilling 62.
+__global__ void __launch_bounds__(kTileRows * kTeam) k_pca_tile(PcaArgs a, TileRows tr, const int64_t *__restrict__ toff,
                                                                 const int32_t *__restrict__ tu,
-                                                                const uint16_t *__restrict__ slot, int64_t tile0,
-                                                                int cap) {
+                                                                const uint16_t *__restrict__ slot, int cap) {
   extern __shared__ double2 s_rec[];  // (x, y)[cap], then z[cap], then code[cap]
   double *s_z = reinterpret_cast<double *>(s_rec + cap);
   uint8_t *s_c = reinterpret_cast<uint8_t *>(s_z + cap);
-  const int64_t tl = xcd_block(blockIdx.x, gridDim.x);
-  const int64_t u0 = toff[tile0 + tl];
-  const int cnt = (int)(toff[tile0 + tl + 1] - u0);
+  // each model is cut into slices for the XCDs by itself (a 3D tile costs four film tiles); the first
+  // takes a multiple of eight blocks, so that the second starts at XCD 0 again
+  const unsigned nt0 = (unsigned)(tr.tile_start[1] - tr.tile_start[0]), n0 = (nt0 + 7u) & ~7u;
+  const bool film = blockIdx.x >= n0;
+  const unsigned tm = film ? xcd_block(blockIdx.x - n0, gridDim.x - n0) : xcd_block(blockIdx.x, n0);
+  if (!film && tm >= nt0) return;  // (the whole block)
+  const int64_t t = tr.tile_start[film] + tm;
+  const int64_t u0 = toff[t];
+  const int cnt = (int)(toff[t + 1] - u0);
   const bool staged = cnt <= cap;
+  const int team = threadIdx.x / kTeam, lane = threadIdx.x % kTeam;
+  const int32_t i = tile_row(tr, t, team);
+  PcaPre<kTeam> pre;
+  if (i >= 0) pre.load(a, slot, i, lane);
   if (staged) {
     const int8_t *kp = a.kind ? a.kind : a.model;  // codes unused without kinds; no branch per load
-    for (int s = threadIdx.x; s < cnt; s += blockDim.x) {
-      const int32_t j = tu[u0 + s];
-      s_rec[s] = make_double2(a.x[j], a.y[j]);
-      s_z[s] = a.z[j];
-      s_c[s] = (uint8_t)pca_code_of(kp[j]);
-    }
+    double v[kStage][3];
+    int8_t k[kStage];
+    stage_tile<kTileRows * kTeam>(
+        tu + u0, cnt,
+        [&](int q, int32_t j) {
+          v[q][0] = a.x[j]; v[q][1] = a.y[j]; v[q][2] = a.z[j];
+          k[q] = kp[j];
+        },
+        [&](int q, int s) {
+          s_rec[s] = make_double2(v[q][0], v[q][1]);
+          s_z[s] = v[q][2];
+          s_c[s] = (uint8_t)(8 * ((k[q] >= 0 && k[q] <= 2) ? k[q] : 3));
+        });
   }
   __syncthreads();
-  const int team = threadIdx.x / kTeam, lane = threadIdx.x % kTeam;
-  const int64_t r = tl * kTileRows + team;
-  if (r >= a.nrows) return;
-  const int32_t i = a.sched[r];
-  if (staged) pca_row<kTeam>(a, i, lane, PcaTile{PcaRec{s_rec, s_z, s_c}, slot});
+  if (i < 0) return;
+  if (staged) pca_row<kTeam>(a, i, lane, PcaTile{PcaRec{s_rec, s_z, s_c}}, &pre);
   else pca_row<kTeam>(a, i, lane, PcaGlobal{});
 }
 
@@ -376,17 +419,20 @@ extern "C" gf_status gf_classify_pca(gf_ctx *ctx, const gf_particles *p, const g
   ProfScope prof(ctx, "pca_cov");
   LaunchUnit units[2 * GF_NBAND];
   const int nu = launch_units(same, units);
+  if (same->ntiles > 0) {
+    const int64_t nt0 = same->tile_start[1] - same->tile_start[0], nt1 = same->tile_start[2] - same->tile_start[1];
+    const int cap = std::min(std::max(same->tile_max[0], same->tile_max[1]), tile_capacity(ctx, kPcaCap));
+    hipLaunchKernelGGL(k_pca_tile, dim3(grid_for((nt0 + 7) / 8 * 8 + nt1, 1)), dim3(kTileRows * kTeam),
+                       (sizeof(double2) + sizeof(double) + 1) * (size_t)cap, ctx->stream, a, tile_rows(same),
+                       same->tile_off, same->tile_u, same->slot, cap);
+    GF_LAUNCH_CHECK(ctx);
+  }
   for (int q = 0; q < nu; ++q) {
     const LaunchUnit &u = units[q];
+    if (u.tiled) continue;
     a.sched = same->grouped + u.row0;
     a.nrows = u.nrows;
-    if (u.tiled) {
-      const int cap = std::min(u.tile_max, tile_capacity(ctx, kPcaCap));
-      hipLaunchKernelGGL(k_pca_tile, dim3(grid_for(u.ntiles, 1)), dim3(kTileRows * kTeam), (sizeof(double2) + sizeof(double) + 1) * (size_t)cap,
-                         ctx->stream, a, same->tile_off, same->tile_u, same->slot, u.tile0, cap);
-    } else {
-      hipLaunchKernelGGL(k_pca_flags, dim3(grid_for(u.nrows * kTeamWide, kBlock)), dim3(kBlock), 0, ctx->stream, a);
-    }
+    hipLaunchKernelGGL(k_pca_flags, dim3(grid_for(u.nrows * kTeamWide, kBlock)), dim3(kBlock), 0, ctx->stream, a);
     GF_LAUNCH_CHECK(ctx);
   }
   }
