@@ -476,7 +476,7 @@ gf_status gf_transition_3d_to_2d_cloud(gf_ctx *ctx, const gf_particles *p, const
 /* ---------------------------------------------------------- adjoints */
 /* Transpose of gf_apply_stencil with respect to u: ubar = C^T ybar, where
  * ybar [K][n] FP64 holds dL/dout; ubar [n] FP64 is overwritten.
- * Deterministic (gathers through the reverse-edge map, no atomics).  With
+ * Deterministic (every sum has a fixed order, no atomics).  With
  * extended neighbourhoods (gf_build_neighbours_rows) the ghost particles,
  * whose rows hold only themselves, receive nothing from the rows that list
  * them; every other term is as for symmetric lists. */

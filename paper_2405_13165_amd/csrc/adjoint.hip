@@ -300,7 +300,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(M =
 
 // A block per tile, a team of kT lanes per row.  The tile's positions and field
 // values are staged in LDS; each lane keeps the dbar of its entries (at most
-// kTileBandRow / kT) in registers, and one component at a time they go to LDS,
+// Q) in registers, and one component at a time they go to LDS,
 // over the staged positions, in tile order, where each distinct neighbour's are
 // added up in row order through the transposed tile.  part: see k_places_sum.
 //
@@ -317,6 +317,11 @@ struct ATile {
   const uint16_t *slot, *tperm, *tself;
   double *part;
 };
+// Entries per lane.  Film rows of at most 64 entries leave registers for a third
+// wave per SIMD: 91 us on 500^2 film rows against 120 (the row kernel took 87 + 29
+// for its gather); 3D rows at three waves spill.
+constexpr int kShortQ = 8, kLongQ = kTileBandRow / kT;
+
 struct AdjTile {
   const double2 *sxy, *szu;
   const double *sh;
@@ -327,11 +332,11 @@ struct AdjTile {
 // the row's end is its last one with weight zero), so that the loads and the
 // long chain of one weight overlap another's.  Returns false where the row
 // contributes nothing (dd is not set).
-template <int M, bool UNI>
+template <int M, int Q, bool UNI>
 __device__ inline bool adj_tile_row(const AArgs &a, const AdjTile &tl, const RowGeom &g, int32_t i, int n, int lane,
                                     double ui, int self, bool on, double (&yb)[4], const double (&xb)[3], double *sm,
-                                    double (&dd)[kTileBandRow / kT][3]) {
-  constexpr int T = kT, Q = kTileBandRow / kT;
+                                    double (&dd)[Q][3]) {
+  constexpr int T = kT;
   const double ir2_row = 1.0 / (g.hi * g.hi);
   uint32_t ss[Q / 2];
   if (on) {
@@ -407,10 +412,10 @@ __device__ inline bool adj_tile_row(const AArgs &a, const AdjTile &tl, const Row
   return true;
 }
 
-template <int M>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+template <int M, int Q>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q > kShortQ ? 2 : 3)))
 k_adjoint_tile(AArgs a, ATile at, int cap) {
-  constexpr int T = kT, Q = kTileBandRow / kT;
+  constexpr int T = kT;
   static_assert(kBlock == kTileRows * kT, "a team per row of the tile");
   extern __shared__ double s_tile[];  // cap x (x, y), cap x (z, u), cap x h; then the terms of one component
   __shared__ double smem[kTileRows * adj_lds_doubles<M>()];
@@ -476,9 +481,9 @@ k_adjoint_tile(AArgs a, ATile at, int cap) {
   double dd[Q][3];
   const AdjTile tile{sxy, szu, sh, at.slot + b};
   if (uni)
-    on = adj_tile_row<M, true>(a, tile, g, i, n, lane, ui, self, on, yb, xb, sm, dd);
+    on = adj_tile_row<M, Q, true>(a, tile, g, i, n, lane, ui, self, on, yb, xb, sm, dd);
   else
-    on = adj_tile_row<M, false>(a, tile, g, i, n, lane, ui, self, on, yb, xb, sm, dd);
+    on = adj_tile_row<M, Q, false>(a, tile, g, i, n, lane, ui, self, on, yb, xb, sm, dd);
   if (!on) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) dd[q][0] = dd[q][1] = dd[q][2] = 0.0;
@@ -596,9 +601,11 @@ extern "C" gf_status gf_gfdm_weights_adjoint(gf_ctx *ctx, const gf_particles *p,
       if (nt <= 0) continue;
       ProfScope prof(ctx, m == 0 ? "weights_adjoint_3d" : "weights_adjoint_film");
       if (m == 0)
-        hipLaunchKernelGGL(k_adjoint_tile<10>, dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
+        hipLaunchKernelGGL((k_adjoint_tile<10, kLongQ>), dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
+      else if (nbr->max_row <= kShortQ * kT)
+        hipLaunchKernelGGL((k_adjoint_tile<6, kShortQ>), dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
       else
-        hipLaunchKernelGGL(k_adjoint_tile<6>, dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
+        hipLaunchKernelGGL((k_adjoint_tile<6, kLongQ>), dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
       GF_LAUNCH_CHECK(ctx);
     }
     ProfScope prof(ctx, "weights_adjoint_gather");

@@ -216,6 +216,8 @@ constexpr int kApplyCap = 2048;
 // the first sum gathered through the reverse-edge map (entry (i,j) sits at
 // rev[k] for the entry k = (j,i) of row j); an entry of row j without a twin
 // (towards a ghost particle, which has no row) adds only its own term.
+// Taken where some row has more than kTileBandRow entries (on the mixed cloud,
+// which has none, 463 us against 206 + 37 over transposed tiles).
 // One team of adj_team lanes per row j (the lanes stride over the row), K the
 // number of selected operators.  Each lane takes adj_unroll entries per step: their
 // columns and twin positions, then their two stencil records (c_ij of row i,
