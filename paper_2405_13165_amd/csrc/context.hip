@@ -35,6 +35,7 @@ extern "C" gf_status gf_create(int device, void *stream, gf_ctx **out) {
   }
   const gf_status st = fixed_scratch_init(ctx);
   if (st != GF_OK) { delete ctx; return st; }
+  if (hipMalloc((void **)&ctx->qpair, 128) != hipSuccess) { delete ctx; return GF_ENOMEM; }
   *out = ctx;
   return GF_OK;
 }
@@ -74,6 +75,7 @@ extern "C" void gf_destroy(gf_ctx *ctx) {
     ctx->pool->blocks.clear();
     ctx->pool->kept = 0;
   }
+  if (ctx->qpair) (void)hipFree(ctx->qpair);  // (waits for the device)
   if (ctx->host_pinned) (void)hipHostFree(ctx->host_pinned);
   if (ctx->stream_order) (void)hipEventDestroy(ctx->stream_order);
   for (auto &r : ctx->prof_pending) {

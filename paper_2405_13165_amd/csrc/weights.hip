@@ -47,6 +47,7 @@ struct WArgs {
   float *kappa_out;
   int32_t *queue;
   int32_t *qcount;
+  int32_t *qreset = nullptr;  // the counter of the next call, cleared by the QR kernel (NULL: none)
   const double *u;
   double *y_out;
   unsigned mask;
@@ -776,6 +777,7 @@ __global__ void __launch_bounds__(kQrBlock) k_weights_qr(WArgs a, double *panels
   __shared__ double vtv[10];
   __shared__ double zt[4][10];
   const int qn = *a.qcount;
+  if (a.qreset && blockIdx.x == 0 && threadIdx.x == 0) *a.qreset = 0;
   for (int q = blockIdx.x; q < qn; q += gridDim.x) {
     const int32_t i = a.queue[q];
     const int64_t b = a.row_ptr[i];
@@ -1125,8 +1127,23 @@ gf_status weights_common(gf_ctx *ctx, const gf_particles *p, const gf_nbr *nbr, 
   a.queue = ws.queue;
   a.qcount = ws.qcount;
   a.u = u; a.y_out = out; a.mask = op_mask;
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, ctx->stream, ws.qcount, 16);
-  GF_LAUNCH_CHECK(ctx);
+  // the context's pair of counters, or, where a graph may run the call at any time, one of the call's own
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  bool pair = !fixed;
+  if (pair && hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    pair = false;
+  }
+  pair = pair && cap == hipStreamCaptureStatusNone;
+  if (pair) {
+    a.qcount = ctx->qpair + 16 * ctx->qnext;
+    a.qreset = ctx->qpair + 16 * (1 - ctx->qnext);
+  }
+  if (!pair || !ctx->qclean) {
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, ctx->stream, pair ? ctx->qpair : ws.qcount, pair ? 32 : 16);
+    GF_LAUNCH_CHECK(ctx);
+  }
+  if (pair) ctx->qclean = false;  // until the QR kernel below is launched
   const bool f32 = wtype == GF_F32;
   if (prec == GF_PLAIN_F64) {
     ProfScope prof(ctx, "weights_plain_f64");
@@ -1165,6 +1182,10 @@ gf_status weights_common(gf_ctx *ctx, const gf_particles *p, const gf_nbr *nbr, 
     }
   }
   GF_LAUNCH_CHECK(ctx);
+  if (pair) {
+    ctx->qclean = true;
+    ctx->qnext = 1 - ctx->qnext;
+  }
   if (stats && !fixed) {
     hipLaunchKernelGGL(k_ls_stats, dim3(1), dim3(1024), 0, ctx->stream, a.status, a.kappa_out, n, ws.counts, ws.kmax);
     GF_LAUNCH_CHECK(ctx);
