@@ -747,8 +747,12 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
         }
         if (none) continue;
         const unsigned nbox = (unsigned)ext[0] * ext[1] * ext[2];  // <= g.nkeys
-        // (a particle lies in its cell's cube up to the rounding of its cell coordinate, below 1e-9 edges)
+        // (a particle lies in its cell's cube up to the rounding of its cell coordinate, below 1e-9 edges; the cubes are
+        // taken from the grid's corner as that coordinate is, so this holds however far the corner is from the origin)
         const double edge = g.edge[ts], Rc = R + 1e-9 * edge;
+        double bl[3];  // the box's centre from the grid's corner
+#pragma unroll
+        for (int d = 0; d < 3; ++d) bl[d] = uniform_f64(bc[d] - g.lo[ts][d]);
 #pragma unroll 1
         for (unsigned kb = 0; kb < nbox; kb += 64) {
           int len = 0, rb = 0;
@@ -762,7 +766,7 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
             double u2 = 0.0;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-              const double lo = fma((double)cc[d], edge, g.lo[ts][d]) - bc[d];  // the cube's faces, from the box's centre
+              const double lo = fma((double)cc[d], edge, -bl[d]);  // the cube's lower face, from the box's centre
               const double below = lo - be[d], above = cc[d] == g.dim[ts][d] - 1 ? 0.0 : -(lo + edge) - be[d];
               const double u = fmax(fmax(below, above), 0.0);
               u2 = fma(u, u, u2);
