@@ -229,10 +229,10 @@ void *nbr_alloc(gf_nbr *nbr, size_t bytes) {
 }
 
 void nbr_release(gf_nbr *nbr) {
-  if (nbr->blocks.empty()) return;
   BlockPool &p = *nbr->pool;
   // work that still reads the lists, on any stream, ends before the blocks are handed out again
-  const bool idle = hipDeviceSynchronize() == hipSuccess;
+  const bool idle = nbr->waiter && hipFree(nbr->waiter) == hipSuccess;
+  nbr->waiter = nullptr;
   std::lock_guard<std::mutex> lock(p.m);
   for (auto &b : nbr->blocks) {
     if (idle && !p.closed && p.kept + b.second <= p.limit) {

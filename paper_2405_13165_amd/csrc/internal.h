@@ -20,9 +20,11 @@
 // hipMalloc / hipFree pair of 128 MiB takes 55 + 235 us here, and far longer now
 // and then).  At most `limit` bytes are kept (1/32 of the device's memory); the
 // context's end gives everything back.  A handle returns its blocks after the
-// device has finished all work (as hipFree waits), so a block taken from here
-// has no pending use on any stream; the lock covers handles freed from other
-// threads.
+// device has finished all work, so a block taken from here has no pending use on
+// any stream; the lock covers handles freed from other threads.  It waits by
+// freeing a small block of its own (0.4 us, as its allocation): hipDeviceSynchronize
+// would end every stream capture under way, hipFree leaves relaxed ones and those
+// of other threads alone.
 struct BlockPool {
   std::mutex m;
   std::vector<std::pair<void *, size_t>> blocks;
@@ -93,6 +95,7 @@ struct gf_nbr {
   // every device array of the handle: (block, bytes) of `pool`
   std::vector<std::pair<void *, size_t>> blocks;
   std::shared_ptr<BlockPool> pool;
+  void *waiter = nullptr;  // freed first, which waits for the device (see BlockPool)
   int device = 0;
   int64_t n = 0;
   int64_t nnz = 0;
