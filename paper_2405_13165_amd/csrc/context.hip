@@ -190,11 +190,20 @@ static size_t block_bytes(size_t bytes) {
   return (bytes + step - 1) / step * step;
 }
 
-void *nbr_alloc(gf_nbr *nbr, size_t bytes) {
+bool capturing(const gf_ctx *ctx) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+
+void *nbr_alloc(gf_nbr *nbr, size_t bytes, bool kept) {
   const size_t need = block_bytes(bytes ? bytes : 1);
   BlockPool &p = *nbr->pool;
   std::pair<void *, size_t> got(nullptr, 0);
-  {
+  if (kept) {
     std::lock_guard<std::mutex> lock(p.m);
     size_t best = p.blocks.size();
     for (size_t k = 0; k < p.blocks.size(); ++k)  // the smallest that fits, at most twice the need
@@ -210,8 +219,9 @@ void *nbr_alloc(gf_nbr *nbr, size_t bytes) {
   if (!got.first) {
     got.second = need;
     if (hipMalloc(&got.first, need) != hipSuccess) {
-      // give the kept blocks back and try once more
       (void)hipGetLastError();
+      if (!kept) return nullptr;
+      // give the kept blocks back and try once more
       {
         std::lock_guard<std::mutex> lock(p.m);
         for (auto &b : p.blocks) (void)hipFree(b.first);

@@ -105,8 +105,15 @@ struct gf_nbr {
   int32_t *col = nullptr;      // [nnz]
   int32_t *grouped = nullptr;  // [n] particles grouped by (model, band), Morton order inside
   int64_t group_start[2 * GF_NBAND + 1] = {0};  // host copy of the group offsets
-  int32_t *rev = nullptr;      // [nnz] position of (j,i) for entry (i,j); built lazily
-  // rows in grouped (Morton) order, built lazily: grow_ptr[t] = entries of the
+  // Maps built at their first use.  `built` says which are there; a call under
+  // stream capture records their kernels into its graph, which may run at any
+  // time or never, and leaves the bit unset, so that the next call builds them
+  // for itself.  (Their memory then is not taken from kept blocks either: what
+  // hipMalloc refuses under capture stays refused.)
+  enum { kRevMap = 1, kGroupedMaps = 2, kTransposed = 4 };
+  unsigned built = 0;
+  int32_t *rev = nullptr;      // [nnz] position of (j,i) for entry (i,j)
+  // rows in grouped (Morton) order: grow_ptr[t] = entries of the
   // rows grouped[0..t), gpos[i] = position of particle i in grouped
   int64_t *grow_ptr = nullptr; // [n+1]
   int32_t *gpos = nullptr;     // [n]
@@ -128,7 +135,7 @@ struct gf_nbr {
   int32_t tile_max[2] = {0};    // host: largest tile list of each model
   int64_t tile_total = 0;       // host: length of tile_u
   int64_t n_rows = 0;           // particles [n_rows, n) are ghosts: their rows hold only themselves
-  // Transposed tiles, built lazily where every row is tiled (max_row <=
+  // Transposed tiles, where every row is tiled (max_row <=
   // kTileBandRow): what the adjoints need to add up, per tile, the entries that
   // refer to one neighbour, and, per particle, its places in the tile lists.
   // A tile's slots, by falling number of entries, are taken in groups of 64; a
@@ -267,8 +274,11 @@ size_t arena_bytes(const std::vector<size_t> &sizes);
 gf_status fixed_scratch_init(gf_ctx *ctx);
 gf_status ensure_scratch(gf_ctx *ctx, size_t bytes, Arena *arena);
 gf_status ensure_host(gf_ctx *ctx, size_t bytes);
-// a device array owned by the handle (released with it); nullptr if there is no memory
-void *nbr_alloc(gf_nbr *nbr, size_t bytes);
+// whether the context's stream is being captured into a graph (or cannot say)
+bool capturing(const gf_ctx *ctx);
+// a device array owned by the handle (released with it); nullptr if there is no memory.
+// kept: one of the context's kept blocks may serve (else always new memory, see gf_nbr::built)
+void *nbr_alloc(gf_nbr *nbr, size_t bytes, bool kept = true);
 // releases every array of the handle
 void nbr_release(gf_nbr *nbr);
 

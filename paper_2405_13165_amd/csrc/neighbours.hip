@@ -1321,9 +1321,14 @@ void free_nbr(gf_nbr *nb) {
 }
 
 template <class T>
-bool take(gf_nbr *nb, T *&p, size_t count) {
-  p = static_cast<T *>(nbr_alloc(nb, sizeof(T) * std::max<size_t>(count, 1)));
+bool take(gf_nbr *nb, T *&p, size_t count, bool kept = true) {
+  p = static_cast<T *>(nbr_alloc(nb, sizeof(T) * std::max<size_t>(count, 1), kept));
   return p != nullptr;
+}
+// the same for an array of the maps built at first use, which a call that failed or was captured may have left
+template <class T>
+bool take_once(gf_nbr *nb, T *&p, size_t count, bool kept) {
+  return p || take(nb, p, count, kept);
 }
 
 }  // namespace
@@ -1357,14 +1362,16 @@ extern "C" gf_status gf_nbr_export(gf_ctx *ctx, const gf_nbr *nbr, int64_t *row_
 }
 
 gf_status ensure_rev(gf_ctx *ctx, gf_nbr *nbr) {
-  if (nbr->rev) return GF_OK;
+  if (nbr->built & gf_nbr::kRevMap) return GF_OK;
   if (nbr->nnz > (int64_t)0x7fffffff)
     return set_error(ctx, GF_ECAPACITY, "the reverse-edge map holds 32-bit positions; %lld entries exceed it",
                      (long long)nbr->nnz);
-  if (!take(nbr, nbr->rev, nbr->nnz)) return set_error(ctx, GF_ENOMEM, "reverse-edge map allocation failed");
+  const bool cap = capturing(ctx);
+  if (!take_once(nbr, nbr->rev, nbr->nnz, !cap)) return set_error(ctx, GF_ENOMEM, "reverse-edge map allocation failed");
   hipLaunchKernelGGL(k_rev, dim3(grid_for(nbr->n * kRevTeam, kBlock)), dim3(kBlock), 0, ctx->stream, nbr->row_ptr, nbr->col,
                      nbr->n, nbr->rev);
   GF_LAUNCH_CHECK(ctx);
+  if (!cap) nbr->built |= gf_nbr::kRevMap;
   return GF_OK;
 }
 
@@ -1401,13 +1408,13 @@ __global__ void __launch_bounds__(kBlock) k_grouped_rev(const int32_t *__restric
 }  // namespace
 
 gf_status ensure_grouped_rows(gf_ctx *ctx, gf_nbr *nbr) {
-  if (nbr->grev) return GF_OK;
+  if (nbr->built & gf_nbr::kGroupedMaps) return GF_OK;
   gf_status st = ensure_rev(ctx, nbr);  // also checks that positions fit 32 bits
   if (st) return st;
   const int64_t n = nbr->n;
-  int32_t *grev = nullptr;  // set in the handle last: it says that the maps are there
-  if ((!nbr->grow_ptr && !take(nbr, nbr->grow_ptr, n + 1)) || (!nbr->gpos && !take(nbr, nbr->gpos, n)) ||
-      !take(nbr, grev, nbr->nnz))
+  const bool cap = capturing(ctx);
+  if (!take_once(nbr, nbr->grow_ptr, n + 1, !cap) || !take_once(nbr, nbr->gpos, n, !cap) ||
+      !take_once(nbr, nbr->grev, nbr->nnz, !cap))
     return set_error(ctx, GF_ENOMEM, "grouped row offsets allocation failed");
   Arena ar;
   if ((st = ensure_scratch(ctx, arena_bytes({sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1)}), &ar)))
@@ -1419,9 +1426,9 @@ gf_status ensure_grouped_rows(gf_ctx *ctx, gf_nbr *nbr) {
   GF_LAUNCH_CHECK(ctx);
   if ((st = scan_i32_to_i64(ctx, len, nbr->grow_ptr, n, tmp))) return st;
   hipLaunchKernelGGL(k_grouped_rev, dim3(grid_for(n * kRevTeam, kBlock)), dim3(kBlock), 0, ctx->stream, nbr->grouped,
-                     nbr->row_ptr, nbr->col, nbr->rev, nbr->grow_ptr, nbr->gpos, n, grev);
+                     nbr->row_ptr, nbr->col, nbr->rev, nbr->grow_ptr, nbr->gpos, n, nbr->grev);
   GF_LAUNCH_CHECK(ctx);
-  nbr->grev = grev;
+  if (!cap) nbr->built |= gf_nbr::kGroupedMaps;
   return GF_OK;
 }
 
@@ -1559,16 +1566,16 @@ __global__ void __launch_bounds__(kBlock) k_places_sort(const int32_t *__restric
 }  // namespace
 
 gf_status ensure_tile_transpose(gf_ctx *ctx, gf_nbr *nb) {
-  if (nb->gidx) return GF_OK;
+  if (nb->built & gf_nbr::kTransposed) return GF_OK;
   if (nb->nnz > (int64_t)0x7fffffff)
     return set_error(ctx, GF_ECAPACITY, "the adjoints' maps hold 32-bit positions; %lld entries exceed them",
                      (long long)nb->nnz);
   const int64_t nt = nb->ntiles, n = nb->n, total = nb->tile_total;
-  int32_t *gidx = nullptr;  // set in the handle last: it says that everything is there
+  const bool cap = capturing(ctx);
   const int64_t room = nb->nnz / 64 + 4 * (total / 64 + nt) + nt * (kTileRows + 1) + 4;  // see k_tile_room
-  if ((!nb->tperm_off && !take(nb, nb->tperm_off, nt + 1)) || (!nb->tperm && !take(nb, nb->tperm, 64 * room)) ||
-      (!nb->tself && !take(nb, nb->tself, kTileRows * nt)) || (!nb->gptr && !take(nb, nb->gptr, n + 1)) ||
-      !take(nb, gidx, total))
+  if (!take_once(nb, nb->tperm_off, nt + 1, !cap) || !take_once(nb, nb->tperm, 64 * room, !cap) ||
+      !take_once(nb, nb->tself, kTileRows * nt, !cap) || !take_once(nb, nb->gptr, n + 1, !cap) ||
+      !take_once(nb, nb->gidx, total, !cap))
     return set_error(ctx, GF_ENOMEM, "transposed tile allocation failed");
   Arena ar;
   gf_status st;
@@ -1586,20 +1593,20 @@ gf_status ensure_tile_transpose(gf_ctx *ctx, gf_nbr *nb) {
                      nb->tile_off, nt, cnt);
   GF_LAUNCH_CHECK(ctx);
   if ((st = scan_i32_to_i64(ctx, cnt, nb->tperm_off, nt, tmp))) return st;
-  const int cap = std::max(nb->tile_max[0], nb->tile_max[1]);
-  const size_t lds = sizeof(uint32_t) * cap + sizeof(uint16_t) * ((cap + 1) & ~1) +
-                     sizeof(uint16_t) * 64 * (1 + 4 * ((cap + 63) / 64) + kTileRows + kTileRows * (size_t)nb->max_row / 64);
+  const int most = std::max(nb->tile_max[0], nb->tile_max[1]);
+  const size_t lds = sizeof(uint32_t) * most + sizeof(uint16_t) * ((most + 1) & ~1) +
+                     sizeof(uint16_t) * 64 * (1 + 4 * ((most + 63) / 64) + kTileRows + kTileRows * (size_t)nb->max_row / 64);
   hipLaunchKernelGGL(k_tile_transpose, dim3((unsigned)nt), dim3(kBlock), lds, sm, tr, nb->row_ptr, nb->col, nb->slot,
-                     nb->tile_off, nb->tperm_off, cap, nb->tperm, nb->tself);
+                     nb->tile_off, nb->tperm_off, most, nb->tperm, nb->tself);
   hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, cnt, n, 0);
   hipLaunchKernelGGL(k_places_count, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, cnt, rank);
   GF_LAUNCH_CHECK(ctx);
   if ((st = scan_i32_to_i32(ctx, cnt, nb->gptr, n, (int32_t *)tmp))) return st;
   hipLaunchKernelGGL(k_places_fill, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, nb->gptr, rank,
                      raw);
-  hipLaunchKernelGGL(k_places_sort, dim3(grid_for(n * 16, kBlock)), dim3(kBlock), 0, sm, nb->gptr, n, raw, gidx);
+  hipLaunchKernelGGL(k_places_sort, dim3(grid_for(n * 16, kBlock)), dim3(kBlock), 0, sm, nb->gptr, n, raw, nb->gidx);
   GF_LAUNCH_CHECK(ctx);
-  nb->gidx = gidx;
+  if (!cap) nb->built |= gf_nbr::kTransposed;
   return GF_OK;
 }
 

@@ -1128,13 +1128,7 @@ gf_status weights_common(gf_ctx *ctx, const gf_particles *p, const gf_nbr *nbr, 
   a.qcount = ws.qcount;
   a.u = u; a.y_out = out; a.mask = op_mask;
   // the context's pair of counters, or, where a graph may run the call at any time, one of the call's own
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  bool pair = !fixed;
-  if (pair && hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    pair = false;
-  }
-  pair = pair && cap == hipStreamCaptureStatusNone;
+  const bool pair = !fixed && !capturing(ctx);
   if (pair) {
     a.qcount = ctx->qpair + 16 * ctx->qnext;
     a.qreset = ctx->qpair + 16 * (1 - ctx->qnext);

@@ -37,3 +37,69 @@ def test_handle_freed_during_a_capture(mode):
         graph.replay()
         torch.cuda.synchronize()
         assert a[0].item() == k + 1
+
+
+def adjoint_setup(kind):
+    """A cloud of tiled rows or with rows beyond the tiles, two handles of it, one call on the second and its results."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx = g.Context(0)
+    d = W.plain_cube(10)
+    if kind == "long rows":
+        d["h"][: d["h"].size // 2] *= 1.4
+    p, nb = built(ctx, d)
+    other = g.build_neighbours(ctx, p)
+    assert (nb.max_row > 128) == (kind == "long rows")
+    w = g.gfdm_weights(ctx, p, nb, g.GF_BATCHED, g.GF_F32)
+    gen = torch.Generator(ctx.device).manual_seed(3)
+    yb = torch.randn((4, p.n), dtype=torch.float64, device=ctx.device, generator=gen)
+    u = torch.randn(p.n, dtype=torch.float64, device=ctx.device, generator=gen)
+    ref = g.apply_stencil_adjoint(ctx, other, w, yb), g.gfdm_weights_adjoint(ctx, p, other, u, yb)
+    return ctx, p, nb, other, w, yb, u, ref
+
+
+@pytest.mark.parametrize("kind", ["tiled", "long rows"])
+def test_first_adjoint_refused_under_capture(kind):
+    """The maps of a handle's first adjoint need memory, which a capture does not allow; kept blocks of the right sizes
+    change nothing, and the handle then works as if it had not been asked."""
+    import ctypes
+    from paper_2405_13165_amd import gfdm as g
+    ctx, p, nb, other, w, yb, u, ref = adjoint_setup(kind)
+    other.close()
+    ub = torch.empty(p.n, dtype=torch.float64, device=ctx.device)
+    hip = ctx.lib  # finds the runtime's own entry points too
+    stream, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(stream), 1) == 0
+    ctx.check(ctx.lib.gf_set_stream(ctx.handle, stream))
+    assert hip.hipStreamBeginCapture(stream, 0) == 0
+    st = ctx.lib.gf_apply_stencil_adjoint(ctx.handle, nb.handle, g.GF_F32, ctypes.c_void_p(w.data_ptr()), 0xF,
+                                          ctypes.c_void_p(yb.data_ptr()), ctypes.c_void_p(ub.data_ptr()))
+    hip.hipStreamEndCapture(stream, ctypes.byref(graph))
+    hip.hipGetLastError()
+    assert st == g.GF_ENOMEM
+    assert torch.equal(g.apply_stencil_adjoint(ctx, nb, w, yb), ref[0])
+    assert torch.equal(g.gfdm_weights_adjoint(ctx, p, nb, u, yb), ref[1])
+    torch.cuda.synchronize()
+    assert hip.hipStreamDestroy(stream) == 0
+
+
+@pytest.mark.parametrize("kind", ["tiled", "long rows"])
+def test_first_adjoint_in_a_relaxed_capture(kind):
+    """A relaxed capture may build the maps in its graph: an eager call before the first replay does not rely on them."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx, p, nb, other, w, yb, u, ref = adjoint_setup(kind)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    xb = torch.zeros((p.n, 3), dtype=torch.float64, device=ctx.device)
+    with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+        ub = g.apply_stencil_adjoint(ctx, nb, w, yb)
+        xb.zero_()
+        g.gfdm_weights_adjoint(ctx, p, nb, u, yb, xbar=xb)
+    for k in range(3):
+        assert torch.equal(g.apply_stencil_adjoint(ctx, nb, w, yb), ref[0])
+        assert torch.equal(g.gfdm_weights_adjoint(ctx, p, nb, u, yb), ref[1])
+        ub.zero_()
+        xb.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ub, ref[0]) and torch.equal(xb, ref[1])
