@@ -313,10 +313,13 @@ __global__ void __launch_bounds__(kBlock) k_keys(const double *__restrict__ x, c
 // one range of the cell order (a multiple of four but for a unit's last, as the
 // search takes rows in fours), and its candidates are read once for all of
 // them.  items[k] = (first row, rows, grid); their order is left to the run (no
-// result depends on it).  Also the units themselves as (first row, rows, grid,
-// cells - 1), those of more than kUnitSmall rows in a list of their own, and the
-// number of particles of each grid.
+// result depends on it).  Also the units of the in-cell order, (first row, rows,
+// grid, cells - 1): such a block, or each of its cells where it holds more than
+// kCellSort particles; those of more than kUnitSmall rows in a list of their own as
+// (first row, rows, grid, piece), a cell of more than kCellSort once for each piece
+// of kCellSort rows.  And the number of particles of each grid.
 constexpr int kUnitSmall = 256;
+constexpr int kCellSort = 2048;
 constexpr int kItemFill = 20;
 constexpr int kItemBits = 3;
 struct CellLists {
@@ -367,9 +370,20 @@ __global__ void __launch_bounds__(kItemsBlock) k_items(const int32_t *__restrict
     s_base[1] = itot ? atomicAdd(out.nitems, itot) : 0;
   }
   __syncthreads();
-  if (len > 0) {
-    int4 *u = small ? out.units + s_base[0] + ub + __popcll(m & ((1ull << lane) - 1ull)) : out.big + atomicAdd(out.nbig, 1);
-    *u = make_int4(a, len, s, cells - 1);
+  if (small) {
+    out.units[s_base[0] + ub + __popcll(m & ((1ull << lane) - 1ull))] = make_int4(a, len, s, cells - 1);
+  } else if (len > 0 && len <= kCellSort) {
+    out.big[atomicAdd(out.nbig, 1)] = make_int4(a, len, s, 0);
+  } else if (len > 0) {
+    for (int c = 0; c < cells; ++c) {
+      const int ca = cell_start[k + c], cl = cell_start[k + c + 1] - ca;
+      if (cl > kUnitSmall) {
+        const int np = (cl + kCellSort - 1) / kCellSort, at = atomicAdd(out.nbig, np);
+        for (int q = 0; q < np; ++q) out.big[at + q] = make_int4(ca, cl, s, q);
+      } else if (cl > 0) {
+        out.units[atomicAdd(out.nunits, 1)] = make_int4(ca, cl, s, 0);
+      }
+    }
   }
   if (parts == 0) return;
   const int at = s_base[1] + ib + inc - parts;
@@ -398,7 +412,6 @@ __global__ void __launch_bounds__(kBlock) k_scatter(const int32_t *__restrict__ 
 // sort and records of the mixed cloud take 16 us (55 before), of the 2.0M jet,
 // whose film comes in no order, 126 us (447 before).
 constexpr int kSubBits = 4;
-constexpr int kCellSort = 2048;
 
 // low kSubBits bits per axis of the fine Morton key, interleaved
 __device__ inline uint32_t fine_sub(double x, double y, double z, const Grid &g, int s) {
@@ -467,8 +480,9 @@ __global__ void __launch_bounds__(64 * kCellSortWaves) k_cell_sort_small(
 }
 
 // Larger units, a block each, by a bitonic network in LDS over the whole fine
-// key; units of more than kCellSort particles keep their order.  The
-// neighbour sets do not depend on this order.
+// key.  The pieces of a cell of more than kCellSort particles leave their keys and
+// indices to k_cell_merge.  The neighbour sets do not depend on this order, but the
+// tiles and so the order of the adjoints' sums do: it is the same for every build.
 __device__ inline uint64_t fine_key(double x, double y, double z, const Grid &g, int s) {
   const double f = (double)(1 << kSubBits);
   int c[3];
@@ -488,49 +502,88 @@ __device__ inline uint64_t fine_key(double x, double y, double z, const Grid &g,
 __global__ void __launch_bounds__(kBlock) k_cell_sort_big(const int4 *__restrict__ units, const int32_t *__restrict__ nunits,
                                                           const double *__restrict__ x, const double *__restrict__ y,
                                                           const double *__restrict__ z, const double *__restrict__ h,
-                                                          Grid g, int32_t *order, double4 *__restrict__ sp) {
+                                                          Grid g, int32_t *order, double4 *__restrict__ sp,
+                                                          uint64_t *__restrict__ skey, int32_t *__restrict__ sid) {
   __shared__ uint64_t kk[kCellSort];
   __shared__ int32_t id[kCellSort];
   const int nu = *nunits;
   for (int u = blockIdx.x; u < nu; u += gridDim.x) {
     const int4 un = units[u];
-    const int b = un.x, len = un.y, s = un.z;
-    if (len <= kCellSort) {
-      int P = 1;
-      while (P < len) P <<= 1;
-      for (int t = threadIdx.x; t < P; t += kBlock) {
-        if (t < len) {
-          const int32_t i = order[b + t];
-          kk[t] = fine_key(x[i], y[i], z[i], g, s);
-          id[t] = i;
-        } else {
-          kk[t] = ~0ull;
-          id[t] = 0x7fffffff;
-        }
+    const int b = un.x + un.w * kCellSort, len = min(kCellSort, un.y - un.w * kCellSort), s = un.z;
+    int P = 1;
+    while (P < len) P <<= 1;
+    for (int t = threadIdx.x; t < P; t += kBlock) {
+      if (t < len) {
+        const int32_t i = order[b + t];
+        kk[t] = fine_key(x[i], y[i], z[i], g, s);
+        id[t] = i;
+      } else {
+        kk[t] = ~0ull;
+        id[t] = 0x7fffffff;
       }
-      __syncthreads();
-      for (int k = 2; k <= P; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-          for (int t = threadIdx.x; t < P; t += kBlock) {
-            const int o = t ^ j;
-            if (o > t) {
-              const uint64_t a = kk[t], e = kk[o];
-              const int32_t ia = id[t], ie = id[o];
-              // ties (same sub-cell) by particle index: the order is deterministic
-              const bool gt = (a > e) || (a == e && ia > ie);
-              if (gt == ((t & k) == 0)) { kk[t] = e; kk[o] = a; id[t] = ie; id[o] = ia; }
-            }
+    }
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1) {
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int t = threadIdx.x; t < P; t += kBlock) {
+          const int o = t ^ j;
+          if (o > t) {
+            const uint64_t a = kk[t], e = kk[o];
+            const int32_t ia = id[t], ie = id[o];
+            // ties (same sub-cell) by particle index: the order is deterministic
+            const bool gt = (a > e) || (a == e && ia > ie);
+            if (gt == ((t & k) == 0)) { kk[t] = e; kk[o] = a; id[t] = ie; id[o] = ia; }
           }
-          __syncthreads();
         }
+        __syncthreads();
       }
     }
     for (int t = threadIdx.x; t < len; t += kBlock) {
-      const int32_t i = len <= kCellSort ? id[t] : order[b + t];
-      if (len <= kCellSort) order[b + t] = i;
+      const int32_t i = id[t];
+      if (un.y > kCellSort) {
+        skey[b + t] = kk[t];
+        sid[b + t] = i;
+        continue;
+      }
+      order[b + t] = i;
       if (sp) sp[b + t] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
     }
     __syncthreads();
+  }
+}
+
+// The sorted pieces of a cell merged, a block per piece: a particle goes behind
+// the smaller ones of every piece, found by binary search.  A million particles in
+// one cell take 488 searches each; the search tests all their pairs.
+__global__ void __launch_bounds__(kBlock) k_cell_merge(const int4 *__restrict__ units, const int32_t *__restrict__ nunits,
+                                                       const double *__restrict__ x, const double *__restrict__ y,
+                                                       const double *__restrict__ z, const double *__restrict__ h,
+                                                       const uint64_t *__restrict__ skey, const int32_t *__restrict__ sid,
+                                                       int32_t *__restrict__ order, double4 *__restrict__ sp) {
+  const int nu = *nunits;
+  for (int u = blockIdx.x; u < nu; u += gridDim.x) {
+    const int4 un = units[u];
+    if (un.y <= kCellSort) continue;
+    const int b = un.x + un.w * kCellSort, len = min(kCellSort, un.y - un.w * kCellSort);
+    for (int t = threadIdx.x; t < len; t += kBlock) {
+      const uint64_t key = skey[b + t];
+      const int32_t i = sid[b + t];
+      int at = un.x + t;
+      for (int o = 0; o * kCellSort < un.y; ++o) {
+        if (o == un.w) continue;
+        const int ob = un.x + o * kCellSort;
+        int lo = 0, hi = min(kCellSort, un.y - o * kCellSort);
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          const uint64_t v = skey[ob + mid];
+          if (v < key || (v == key && sid[ob + mid] < i)) lo = mid + 1;
+          else hi = mid;
+        }
+        at += lo;
+      }
+      order[at] = i;
+      if (sp) sp[at] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
+    }
   }
 }
 
@@ -1793,7 +1846,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
         sizeof(double4) * (n + kRowPad), sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1),
         sizeof(int32_t) * 32, sizeof(int32_t) * n, sizeof(int32_t) * (n + 1), sizeof(int32_t) * scan_tmp_elems(n + 1),
         sizeof(int32_t) * n, sizeof(int4) * n, sizeof(int4) * n, sizeof(int4) * (n / kUnitSmall + 1),
-        sizeof(int32_t) * (n + kRowPad)};
+        sizeof(int32_t) * (n + kRowPad), sizeof(uint64_t) * (n > kCellSort ? n : 0)};
   // rows staged by the count pass (sw entries each, the widest that stays
   // under 8 GB); rows found longer are filled by a second search pass
   int sw = 0;
@@ -1821,6 +1874,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   int4 *units = ar.take<int4>(n);
   int4 *big = ar.take<int4>(n / kUnitSmall + 1);
   int32_t *order = ar.take<int32_t>(n + kRowPad);  // particles in cell order
+  uint64_t *skey = ar.take<uint64_t>(n > kCellSort ? n : 0);  // keys of the pieces of very full cells
   int32_t *stage = use_stage ? ar.take<int32_t>((size_t)n * sw) : nullptr;
 
   gf_nbr *nb = new gf_nbr();
@@ -1851,7 +1905,10 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
                        dim3(64 * kCellSortWaves), 0, sm, lists.units, lists.nunits, key, p->x, p->y, p->z, p->h, gg, ord,
                        recs);
     hipLaunchKernelGGL(k_cell_sort_big, dim3((unsigned)std::min<int64_t>(n / kUnitSmall + 1, 4 * ctx->num_cu)),
-                       dim3(kBlock), 0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, gg, ord, recs);
+                       dim3(kBlock), 0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, gg, ord, recs, skey, slot);
+    if (n > kCellSort)  // (slot[] is free after the scatter)
+      hipLaunchKernelGGL(k_cell_merge, dim3((unsigned)std::min<int64_t>(n / kCellSort + 1, 4 * ctx->num_cu)), dim3(kBlock),
+                         0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, skey, slot, ord, recs);
     return hipGetLastError() == hipSuccess ? GF_OK : set_error(ctx, GF_EHIP, "cell order kernels failed");
   };
   {

@@ -36,3 +36,37 @@ def pairs_at_faces(origin):
 def test_far_from_the_origin(origin):
     """Coordinates large against the supports (2^43: positions known to 2e-3 supports)."""
     check(pairs_at_faces(origin))
+
+
+def far_cubes(size):
+    """Two jittered cubes of size^3 particles 1e5 supports apart, in no order: the cells are wider than a cube of 12^3
+    (1,728 particles; blocks of eight cells hold more) and hold up to several thousand of a cube of 24^3."""
+    rng = np.random.default_rng([5, size])
+    a = np.stack(W.jittered_cube(size, 1.0, rng), 1)
+    b = np.stack(W.jittered_cube(size, 1.0, rng), 1) + [2.6e5, 0.0, 0.0]
+    pos = np.concatenate([a, b])[rng.permutation(2 * len(a))]
+    n = len(pos)
+    return W._pack(pos[:, 0], pos[:, 1], pos[:, 2], np.full(n, 2.6), np.zeros(n), np.zeros(n))
+
+
+@pytest.mark.parametrize("size", [12, 14, 24])
+def test_full_cells(size):
+    """Cells and blocks of cells of more than 2,048 particles: the lists, and adjoints that are the same for every build of
+    the cloud (their sums follow the order of the cells)."""
+    import torch
+    from paper_2405_13165_amd import gfdm as g
+    d = far_cubes(size)
+    check(d)
+    ctx = g.Context(0)
+    p = g.Particles.from_dict(ctx, d)
+    gen = torch.Generator(ctx.device).manual_seed(size)
+    yb = torch.randn((4, p.n), dtype=torch.float64, device=ctx.device, generator=gen)
+    u = torch.randn(p.n, dtype=torch.float64, device=ctx.device, generator=gen)
+    first = None
+    for _ in range(4):
+        nb = g.build_neighbours(ctx, p)
+        assert nb.max_row <= 128
+        w = g.gfdm_weights(ctx, p, nb, g.GF_BATCHED, g.GF_F64)
+        got = w, g.apply_stencil_adjoint(ctx, nb, w, yb), g.gfdm_weights_adjoint(ctx, p, nb, u, yb)
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(first, got))
