@@ -208,6 +208,7 @@ __global__ void __launch_bounds__(kBboxFin) k_bbox_final(const double *__restric
 // candidate sets of the others.
 constexpr int kMaxLevels = 4;
 constexpr int kMaxSlots = 2 * kMaxLevels;
+constexpr int kMaxAxis = 1000000;  // cells per axis, at most: the last one also holds what lies beyond it
 struct Grid {
   int nslots;
   int slot0[3];              // slots of model m: [slot0[m], slot0[m + 1])
@@ -794,8 +795,8 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
           const double f0 = floor((b0[d] - R - g.lo[ts][d]) * g.inv_edge[ts]);
           const double f1 = floor((b1[d] + R - g.lo[ts][d]) * g.inv_edge[ts]);
           const double top = (double)(g.dim[ts][d] - 1);
-          none = none || f1 < 0.0 || f0 > top;
-          a0[d] = __builtin_amdgcn_readfirstlane((int)fmax(f0, 0.0));
+          none = none || f1 < 0.0 || (f0 > top && g.dim[ts][d] < kMaxAxis);
+          a0[d] = __builtin_amdgcn_readfirstlane((int)fmin(fmax(f0, 0.0), top));
           ext[d] = __builtin_amdgcn_readfirstlane((int)fmin(f1, top)) - a0[d] + 1;
         }
         if (none) continue;
@@ -813,8 +814,7 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
           if (kc < nbox) {
             const unsigned q = kc / ext[0], qq = q / ext[1];
             const int cx = a0[0] + (int)(kc - q * ext[0]), cy = a0[1] + (int)(q - qq * ext[1]), cz = a0[2] + (int)qq;
-            // distance of the cell's cube to the box; the last cell of an axis also holds what lies beyond
-            // it (a grid has at most 10^6 cells per axis)
+            // distance of the cell's cube to the box; the last cell of an axis also holds what lies beyond it
             const int cc[3] = {cx, cy, cz};
             double u2 = 0.0;
 #pragma unroll
@@ -1820,7 +1820,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
         for (int d = 0; d < 3; ++d) {
           double span = empty ? 0.0 : hi[m][d] - lo[m][d];
           double dd = std::floor(span / edge) + 1.0;
-          if (dd > 1e6) dd = 1e6;
+          if (dd > kMaxAxis) dd = kMaxAxis;
           g.dim[ns][d] = (int)dd;
           g.bits[ns][d] = ceil_log2(g.dim[ns][d]);
           tb += g.bits[ns][d];

@@ -70,3 +70,15 @@ def test_full_cells(size):
         got = w, g.apply_stencil_adjoint(ctx, nb, w, yb), g.gfdm_weights_adjoint(ctx, p, nb, u, yb)
         first = first or got
         assert all(torch.equal(a, b) for a, b in zip(first, got))
+
+
+def test_longer_than_a_grid():
+    """Pairs along a line of 1.009 million supports: a grid has at most 10^6 cells per axis (reached from 262,144 particles
+    on), and 2,402 particles lie beyond its last one."""
+    k = np.arange(131_072)
+    x = np.concatenate([7.7 * k, 7.7 * k + 0.9])
+    z = np.zeros(x.size)
+    d = W._pack(x, z, z, np.ones(x.size), z, z)
+    assert (x > 1e6 * (1 + 1e-9)).sum() == 2402
+    check(d)
+    check(d, n_rows=x.size - 1000)
