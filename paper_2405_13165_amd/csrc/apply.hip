@@ -462,8 +462,8 @@ gf_status launch_apply(gf_ctx *ctx, const gf_nbr *nbr, const void *w, unsigned m
 // Team-size search for the application kernel (FP64 field), per launch unit.
 gf_status tune_apply(gf_ctx *ctx, const gf_nbr *nbr, const void *w, gf_dtype wtype) {
   double *u = nullptr, *out = nullptr;
-  if (hipMalloc(&u, sizeof(double) * nbr->n) != hipSuccess) return set_error(ctx, GF_ENOMEM, "tuning buffer");
-  if (hipMalloc(&out, sizeof(double) * 4 * nbr->n) != hipSuccess) {
+  if (!device_alloc(*ctx->pool, (void **)&u, sizeof(double) * nbr->n)) return set_error(ctx, GF_ENOMEM, "tuning buffer");
+  if (!device_alloc(*ctx->pool, (void **)&out, sizeof(double) * 4 * nbr->n)) {
     (void)hipFree(u);
     return set_error(ctx, GF_ENOMEM, "tuning buffer");
   }

@@ -162,6 +162,24 @@ size_t arena_bytes(const std::vector<size_t> &sizes) {
   return t;
 }
 
+bool device_alloc(BlockPool &p, void **out, size_t bytes) {
+  hipError_t e = hipMalloc(out, bytes);
+  if (e == hipErrorOutOfMemory) {  // (under capture it is refused otherwise)
+    (void)hipGetLastError();
+    {
+      std::lock_guard<std::mutex> lock(p.m);
+      for (auto &b : p.blocks) (void)hipFree(b.first);
+      p.blocks.clear();
+      p.kept = 0;
+    }
+    e = hipMalloc(out, bytes);
+  }
+  if (e == hipSuccess) return true;
+  (void)hipGetLastError();
+  *out = nullptr;
+  return false;
+}
+
 gf_status ensure_scratch(gf_ctx *ctx, size_t bytes, Arena *arena) {
   if (bytes > ctx->scratch_bytes) {
     if (ctx->scratch) {
@@ -171,8 +189,7 @@ gf_status ensure_scratch(gf_ctx *ctx, size_t bytes, Arena *arena) {
       ctx->scratch_bytes = 0;
     }
     size_t want = bytes + bytes / 4 + (1 << 20);
-    if (hipMalloc(&ctx->scratch, want) != hipSuccess) {
-      ctx->scratch = nullptr;
+    if (!device_alloc(*ctx->pool, &ctx->scratch, want)) {
       return set_error(ctx, GF_ENOMEM, "scratch allocation of %zu bytes failed", want);
     }
     ctx->scratch_bytes = want;
@@ -218,21 +235,7 @@ void *nbr_alloc(gf_nbr *nbr, size_t bytes, bool kept) {
   }
   if (!got.first) {
     got.second = need;
-    if (hipMalloc(&got.first, need) != hipSuccess) {
-      (void)hipGetLastError();
-      if (!kept) return nullptr;
-      // give the kept blocks back and try once more
-      {
-        std::lock_guard<std::mutex> lock(p.m);
-        for (auto &b : p.blocks) (void)hipFree(b.first);
-        p.blocks.clear();
-        p.kept = 0;
-      }
-      if (hipMalloc(&got.first, need) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-      }
-    }
+    if (!device_alloc(p, &got.first, need)) return nullptr;
   }
   nbr->blocks.push_back(got);
   return got.first;

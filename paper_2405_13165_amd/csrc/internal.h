@@ -274,6 +274,8 @@ size_t arena_bytes(const std::vector<size_t> &sizes);
 gf_status fixed_scratch_init(gf_ctx *ctx);
 gf_status ensure_scratch(gf_ctx *ctx, size_t bytes, Arena *arena);
 gf_status ensure_host(gf_ctx *ctx, size_t bytes);
+// hipMalloc; where there is no memory, once more after the kept blocks of freed handles went back
+bool device_alloc(BlockPool &pool, void **p, size_t bytes);
 // whether the context's stream is being captured into a graph (or cannot say)
 bool capturing(const gf_ctx *ctx);
 // a device array owned by the handle (released with it); nullptr if there is no memory.

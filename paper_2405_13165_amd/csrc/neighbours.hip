@@ -1884,8 +1884,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   nb->n_rows = n_rows;
   nb->cross = cross_model ? 1 : 0;
   auto fail = [&](gf_status s2) { free_nbr(nb); return s2; };
-  if (hipMalloc(&nb->waiter, 4096) != hipSuccess) nb->waiter = nullptr;
-  if (!nb->waiter || !take(nb, nb->row_ptr, n + 1) || !take(nb, nb->grouped, n))
+  if (!device_alloc(*ctx->pool, &nb->waiter, 4096) || !take(nb, nb->row_ptr, n + 1) || !take(nb, nb->grouped, n))
     return fail(set_error(ctx, GF_ENOMEM, "neighbour handle allocation failed"));
 
   // The particles in the order of a grid's cells (fine Morton order inside them), the units and, with them, the

@@ -1272,7 +1272,7 @@ extern "C" gf_status gf_autotune(gf_ctx *ctx, const gf_particles *p, const gf_nb
   const int64_t n = p->n;
   const size_t wbytes = (size_t)std::max<int64_t>(nbr->nnz, 1) * 4 * (wtype == GF_F32 ? sizeof(float) : sizeof(double));
   void *wbuf = nullptr;
-  if (hipMalloc(&wbuf, wbytes) != hipSuccess) return set_error(ctx, GF_ENOMEM, "autotune buffer allocation failed");
+  if (!device_alloc(*ctx->pool, &wbuf, wbytes)) return set_error(ctx, GF_ENOMEM, "autotune buffer allocation failed");
   Arena ar;
   if ((st = ensure_scratch(ctx, arena_bytes({sizeof(int32_t) * n, 64, sizeof(double4) * n, sizeof(double) * n,
                                              sizeof(double) * 4 * n}), &ar))) {
