@@ -248,12 +248,17 @@ void nbr_release(gf_nbr *nbr) {
   nbr->waiter = nullptr;
   std::lock_guard<std::mutex> lock(p.m);
   for (auto &b : nbr->blocks) {
-    if (idle && !p.closed && p.kept + b.second <= p.limit) {
-      p.blocks.push_back(b);
-      p.kept += b.second;
-    } else {
+    if (!idle || p.closed || b.second > p.limit) {
       (void)hipFree(b.first);
+      continue;
     }
+    while (p.kept + b.second > p.limit) {  // the oldest make room: the next handle will be like the last
+      (void)hipFree(p.blocks.front().first);
+      p.kept -= p.blocks.front().second;
+      p.blocks.erase(p.blocks.begin());
+    }
+    p.blocks.push_back(b);
+    p.kept += b.second;
   }
   nbr->blocks.clear();
 }

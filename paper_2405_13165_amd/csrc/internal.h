@@ -18,8 +18,8 @@
 // for its next ones.  A simulation builds and frees its lists every step, and
 // the driver's own calls cost more than the build's kernels on small clouds (a
 // hipMalloc / hipFree pair of 128 MiB takes 55 + 235 us here, and far longer now
-// and then).  At most `limit` bytes are kept (1/32 of the device's memory); the
-// context's end gives everything back.  A handle returns its blocks after the
+// and then).  At most `limit` bytes are kept (1/32 of the device's memory), the last
+// ones freed; the context's end gives everything back.  A handle returns its blocks after the
 // device has finished all work, so a block taken from here has no pending use on
 // any stream; the lock covers handles freed from other threads.  It waits by
 // freeing a small block of its own (0.4 us, as its allocation): hipDeviceSynchronize

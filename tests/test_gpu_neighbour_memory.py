@@ -131,3 +131,22 @@ def test_kept_memory_serves_the_scratch():
     finally:
         del fill
         torch.cuda.empty_cache()
+
+
+def test_kept_memory_follows_the_clouds():
+    """With the kept memory full of another cloud's blocks (1/32 of the device, 45 handles of 0.3 GB and more freed), a
+    smaller cloud's next handle still finds the blocks of its last one (its lists between the sizes of the others' arrays) and
+    takes no new memory."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx = g.Context(0)
+    pa = g.Particles.from_dict(ctx, W.plain_cube(80))
+    pb = g.Particles.from_dict(ctx, W.plain_cube(45))
+    handles = [g.build_neighbours(ctx, pa) for _ in range(45)]
+    assert 45 * 6 * handles[0].nnz > torch.cuda.get_device_properties(ctx.device).total_memory / 32
+    for h in handles:
+        h.close()
+    g.build_neighbours(ctx, pb).close()
+    before = torch.cuda.mem_get_info(ctx.device)[0]
+    nb = g.build_neighbours(ctx, pb)
+    assert before - torch.cuda.mem_get_info(ctx.device)[0] < nb.nnz
+    nb.close()
