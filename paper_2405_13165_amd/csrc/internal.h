@@ -148,7 +148,7 @@ struct gf_nbr {
   int64_t *tperm_off = nullptr;  // [ntiles + 1] first of each tile's block, in units of 64
   uint16_t *tperm = nullptr;     // [64 tperm_off[ntiles]]
   uint16_t *tself = nullptr;     // [kTileRows ntiles] slot of each team's own particle
-  int32_t *gptr = nullptr;      // [n + 1] places of each particle in tile_u ...
+  int32_t *gptr = nullptr;      // [n + 1] places of each particle in tile_u (ghosts: none) ...
   int32_t *gidx = nullptr;      // [tile_total] ... ascending
 };
 constexpr int kTileRows = 32;

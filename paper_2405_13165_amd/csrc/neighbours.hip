@@ -1588,17 +1588,20 @@ __global__ void __launch_bounds__(kBlock) k_tile_transpose(TileRows tr, const in
   for (int k = threadIdx.x; k < 32 * (1 + G + S); k += kBlock) out[k] = reinterpret_cast<const uint32_t *>(s_out)[k];
 }
 
-// places of each particle, and the order in which they came (whatever it was)
-__global__ void __launch_bounds__(kBlock) k_places_count(const int32_t *__restrict__ tile_u, int64_t total,
+// places of each particle, and the order in which they came (whatever it was).
+// Ghost particles receive nothing, so their places are left out: a row's
+// neighbours list it in turn and are at most kTileBandRow, but a ghost can be in
+// the rows of any number of others.
+__global__ void __launch_bounds__(kBlock) k_places_count(const int32_t *__restrict__ tile_u, int64_t total, int64_t n_rows,
                                                          int32_t *__restrict__ cnt, int32_t *__restrict__ rank) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < total) rank[k] = atomicAdd(&cnt[tile_u[k]], 1);
+  if (k < total && tile_u[k] < n_rows) rank[k] = atomicAdd(&cnt[tile_u[k]], 1);
 }
-__global__ void __launch_bounds__(kBlock) k_places_fill(const int32_t *__restrict__ tile_u, int64_t total,
+__global__ void __launch_bounds__(kBlock) k_places_fill(const int32_t *__restrict__ tile_u, int64_t total, int64_t n_rows,
                                                         const int32_t *__restrict__ gptr,
                                                         const int32_t *__restrict__ rank, int32_t *__restrict__ raw) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < total) raw[gptr[tile_u[k]] + rank[k]] = (int32_t)k;
+  if (k < total && tile_u[k] < n_rows) raw[gptr[tile_u[k]] + rank[k]] = (int32_t)k;
 }
 // each particle's places ascending (a few tens): a place goes after the smaller ones
 __global__ void __launch_bounds__(kBlock) k_places_sort(const int32_t *__restrict__ gptr, int64_t n,
@@ -1652,11 +1655,12 @@ gf_status ensure_tile_transpose(gf_ctx *ctx, gf_nbr *nb) {
   hipLaunchKernelGGL(k_tile_transpose, dim3((unsigned)nt), dim3(kBlock), lds, sm, tr, nb->row_ptr, nb->col, nb->slot,
                      nb->tile_off, nb->tperm_off, most, nb->tperm, nb->tself);
   hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, cnt, n, 0);
-  hipLaunchKernelGGL(k_places_count, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, cnt, rank);
+  hipLaunchKernelGGL(k_places_count, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, nb->n_rows, cnt,
+                     rank);
   GF_LAUNCH_CHECK(ctx);
   if ((st = scan_i32_to_i32(ctx, cnt, nb->gptr, n, (int32_t *)tmp))) return st;
-  hipLaunchKernelGGL(k_places_fill, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, nb->gptr, rank,
-                     raw);
+  hipLaunchKernelGGL(k_places_fill, dim3(grid_for(total, kBlock)), dim3(kBlock), 0, sm, nb->tile_u, total, nb->n_rows,
+                     nb->gptr, rank, raw);
   hipLaunchKernelGGL(k_places_sort, dim3(grid_for(n * 16, kBlock)), dim3(kBlock), 0, sm, nb->gptr, n, raw, nb->gidx);
   GF_LAUNCH_CHECK(ctx);
   if (!cap) nb->built |= gf_nbr::kTransposed;

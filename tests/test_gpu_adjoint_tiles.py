@@ -79,3 +79,43 @@ def test_apply_rows_at_every_offset():
                 y = g.apply_stencil(ctx, nb, w, torch.as_tensor(u, device=ctx.device).float(), op_mask=mask)
                 ref = oracle.apply(rp, col, w64, u.astype(np.float32).astype(np.float64), op_mask=mask)
                 assert np.abs(y.cpu().numpy() - ref).max() <= 2e-6 * np.abs(ref).max()
+
+
+def test_ghosts_in_every_row():
+    """A film of 250,000 particles with two ghosts that every row lists: the application's adjoint to 1e-12 of its largest
+    value (ghosts receive nothing), and a first call, with its maps, that does not grow with the square of the tiles (7,813):
+    within ten times that of ghosts with ordinary supports."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx = g.Context(0)
+    rng = np.random.default_rng(8)
+    i, j = (a.ravel() for a in np.meshgrid(np.arange(500), np.arange(500), indexing="ij"))
+    x = np.append(i + rng.uniform(-0.2, 0.2, i.size), [250.2, 250.7])
+    y = np.append(j + rng.uniform(-0.2, 0.2, i.size), [250.6, 250.1])
+    z = np.zeros(x.size)
+    n_rows = x.size - 2
+    took = []
+    for reach in (3.0, 2000.0):
+        h = np.append(np.full(n_rows, 3.0), [reach, reach])
+        d = W._pack(x, y, z, h, np.ones(x.size), np.full(x.size, W.WALL), z, z, z + 1)
+        p = g.Particles.from_dict(ctx, d)
+        nb = g.build_neighbours(ctx, p, n_rows=n_rows)
+        w = g.gfdm_weights(ctx, p, nb, g.GF_BATCHED, g.GF_F64)
+        yb = torch.as_tensor(rng.standard_normal((1, p.n)), device=ctx.device)
+        g.apply_stencil_adjoint(ctx, nb, w, yb, op_mask=0x8)
+        times = []
+        for _ in range(3):
+            again = g.build_neighbours(ctx, p, n_rows=n_rows)
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            ub = g.apply_stencil_adjoint(ctx, again, w, yb, op_mask=0x8)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took.append(sorted(times)[1])
+        rp, col = (t.cpu().numpy() for t in nb.export())
+        assert (np.bincount(col)[n_rows:] > n_rows).all() == (reach > 3.0)
+        ub_o = oracle.apply_adjoint(rp, col, w.cpu().numpy(), yb.cpu().numpy(), op_mask=0x8)
+        ub = ub.cpu().numpy()
+        assert (ub[n_rows:] == 0.0).all()
+        assert np.abs(ub - ub_o)[:n_rows].max() <= 1e-12 * np.abs(ub_o[:n_rows]).max()
+    assert took[1] < 10.0 * took[0]
