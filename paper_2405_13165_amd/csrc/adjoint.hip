@@ -317,9 +317,10 @@ struct ATile {
   const uint16_t *slot, *tperm, *tself;
   double *part;
 };
-// Entries per lane.  Film rows of at most 64 entries leave registers for a third
-// wave per SIMD: 91 us on 500^2 film rows against 120 (the row kernel took 87 + 29
-// for its gather); 3D rows at three waves spill.
+// Entries per lane.  Film rows of at most 64 entries, by the film's own longest
+// row, leave registers for a third wave per SIMD: 159 us on 500^2 film rows of 28
+// entries against 220 (the row kernel of before took 168 to 246 by the operators,
+// and about 50 for its gather); 3D rows at three waves spill.
 constexpr int kShortQ = 8, kLongQ = kTileBandRow / kT;
 
 struct AdjTile {
@@ -586,7 +587,7 @@ extern "C" gf_status gf_gfdm_weights_adjoint(gf_ctx *ctx, const gf_particles *p,
   a.mask = op_mask; a.u = u; a.ybar = ybar; a.status = status_n;
   a.xbar = xbar_3n;
   Arena ar;
-  auto lds = [&](int m) { return std::max(kTilePart * (size_t)nbr->tile_max[m], sizeof(double) * (kTileRows * (size_t)nbr->max_row + 1)); };
+  auto lds = [&](int m) { return std::max(kTilePart * (size_t)nbr->tile_max[m], sizeof(double) * (kTileRows * (size_t)nbr->model_row[m] + 1)); };
   if (all_tiled(nbr) && std::max(lds(0), lds(1)) <= kAdjTileLds) {
     if ((st = ensure_tile_transpose(ctx, const_cast<gf_nbr *>(nbr)))) return st;
     if ((st = ensure_scratch(ctx, arena_bytes({sizeof(double) * 3 * (size_t)nbr->tile_total}), &ar))) return st;
@@ -602,7 +603,7 @@ extern "C" gf_status gf_gfdm_weights_adjoint(gf_ctx *ctx, const gf_particles *p,
       ProfScope prof(ctx, m == 0 ? "weights_adjoint_3d" : "weights_adjoint_film");
       if (m == 0)
         hipLaunchKernelGGL((k_adjoint_tile<10, kLongQ>), dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
-      else if (nbr->max_row <= kShortQ * kT)
+      else if (nbr->model_row[1] <= kShortQ * kT)
         hipLaunchKernelGGL((k_adjoint_tile<6, kShortQ>), dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);
       else
         hipLaunchKernelGGL((k_adjoint_tile<6, kLongQ>), dim3((unsigned)nt), dim3(kBlock), lds(m), ctx->stream, a, at, nbr->tile_max[m]);

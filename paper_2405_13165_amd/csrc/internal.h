@@ -100,6 +100,7 @@ struct gf_nbr {
   int64_t n = 0;
   int64_t nnz = 0;
   int32_t max_row = 0;
+  int32_t model_row[2] = {0};  // longest row of each model
   int cross = 0;
   int64_t *row_ptr = nullptr;  // [n+1]
   int32_t *col = nullptr;      // [nnz]

@@ -671,19 +671,19 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
                                                          const int32_t *__restrict__ slot_count,
                                                          int64_t n_rows, Grid g, int cross,
                                                          int32_t *__restrict__ cnt, int32_t *__restrict__ hist,
-                                                         int32_t *__restrict__ maxrow,
+                                                         int32_t *__restrict__ maxrow,  // [2] per model
                                                          const int64_t *__restrict__ row_ptr,
                                                          int32_t *__restrict__ col, int32_t *__restrict__ stage,
                                                          int sw) {
   __shared__ double2 s_xy[kSearchWaves][kRing], s_zh[kSearchWaves][kRing];  // the ring: positions, half supports,
   __shared__ int32_t s_id[kSearchWaves][kRing];                             // user indices
   __shared__ int32_t s_mark[kSearchWaves][64];
-  __shared__ int32_t s_hist[2 * GF_NBAND + 1];
+  __shared__ int32_t s_hist[2 * GF_NBAND + 2];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ni = *nitems;
-  if (MODE != 1 && tid <= 2 * GF_NBAND) s_hist[tid] = 0;
+  if (MODE != 1 && tid < 2 * GF_NBAND + 2) s_hist[tid] = 0;
   int hist_local = 0;  // lane b < 2*GF_NBAND: rows counted in bin b (MODE 0)
-  int max_local = 0;
+  int max_local[2] = {0, 0};
   const int nx = gridDim.x % 8 == 0 ? 8 : 1;
   const int xcd = blockIdx.x % nx, G = gridDim.x / nx * kSearchWaves;
   constexpr bool STORE = MODE != 0;
@@ -897,7 +897,8 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
         int band = 0;
         while (band < GF_NBAND - 1 && cc > kBandHi[band]) ++band;
         bin = mrow * GF_NBAND + band;
-        max_local = max(max_local, cc);
+        max_local[0] = max(max_local[0], mrow ? 0 : cc);
+        max_local[1] = max(max_local[1], mrow ? cc : 0);
       }
       // per-wave histogram, all lanes active: lane b counts bin b
 #pragma unroll
@@ -911,13 +912,16 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
     // one atomic per block and bin (a few addresses for the whole grid)
     __syncthreads();
     if (lane < 2 * GF_NBAND && hist_local) atomicAdd(&s_hist[lane], hist_local);
-    int cm = max_local;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cm = max(cm, __shfl_xor(cm, o, 64));
-    if (lane == 0) atomicMax(&s_hist[2 * GF_NBAND], cm);
+    for (int m = 0; m < 2; ++m) {
+      int cm = max_local[m];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) cm = max(cm, __shfl_xor(cm, o, 64));
+      if (lane == 0) atomicMax(&s_hist[2 * GF_NBAND + m], cm);
+    }
     __syncthreads();
     if (tid < 2 * GF_NBAND && s_hist[tid]) atomicAdd(&hist[tid], s_hist[tid]);
-    if (tid == 2 * GF_NBAND && s_hist[tid]) atomicMax(maxrow, s_hist[tid]);
+    if (tid >= 2 * GF_NBAND && tid < 2 * GF_NBAND + 2 && s_hist[tid]) atomicMax(&maxrow[tid - 2 * GF_NBAND], s_hist[tid]);
   }
 }
 
@@ -1866,7 +1870,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   double4 *sp = ar.take<double4>(n + kRowPad);
   int32_t *cnt = ar.take<int32_t>(n);
   int64_t *tmp64 = ar.take<int64_t>(scan_tmp_elems(n + 1));
-  // hist[8], maxrow, -, search items, units and big units [10 .. 12], units and big units of the second order
+  // hist[8], longest row per model [8], [9], search items, units and big units [10 .. 12], units and big units of the second order
   // [13], [14], particles per grid [16 .. 16 + kMaxSlots); zeroed before use
   int32_t *small = ar.take<int32_t>(32);
   int32_t *slot_count = small + 16;
@@ -1930,7 +1934,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   }
   if (hipGetLastError() != hipSuccess) return fail(set_error(ctx, GF_EHIP, "count kernel launch failed"));
   if ((st = scan_i32_to_i64(ctx, cnt, nb->row_ptr, n, tmp64))) return fail(st);
-  const int64_t *hs = (const int64_t *)ctx->host_pinned;  // histogram, longest row, -, entries
+  const int64_t *hs = (const int64_t *)ctx->host_pinned;  // histogram, longest rows, entries
   hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, sm, small, 10, nb->row_ptr + n, (int64_t *)ctx->host_pinned);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(sm) != hipSuccess)
     return fail(set_error(ctx, GF_EHIP, "read-back of neighbour counts failed"));
@@ -1943,7 +1947,8 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
       hist[m * GF_NBAND + kTileBand] += hist[m * GF_NBAND + band];
       hist[m * GF_NBAND + band] = 0;
     }
-  nb->max_row = (int32_t)hs[8];
+  for (int m = 0; m < 2; ++m) nb->model_row[m] = (int32_t)hs[8 + m];
+  nb->max_row = std::max(nb->model_row[0], nb->model_row[1]);
   nb->nnz = hs[10];
   if (nb->max_row > kMaxRow)
     return fail(set_error(ctx, GF_ECAPACITY, "a particle has %d neighbours; the limit is %d", nb->max_row, kMaxRow));

@@ -119,3 +119,47 @@ def test_ghosts_in_every_row():
         assert (ub[n_rows:] == 0.0).all()
         assert np.abs(ub - ub_o)[:n_rows].max() <= 1e-12 * np.abs(ub_o[:n_rows]).max()
     assert took[1] < 10.0 * took[0]
+
+
+def film_cloud(nx, rng):
+    i, j = (a.ravel() for a in np.meshgrid(np.arange(nx), np.arange(nx), indexing="ij"))
+    x, y = i + rng.uniform(-0.2, 0.2, i.size), j + rng.uniform(-0.2, 0.2, i.size)
+    z = np.zeros(i.size)
+    return W._pack(x, y, z, np.full(i.size, 3.0), np.ones(i.size), np.full(i.size, W.WALL), z, z, z + 1)
+
+
+def with_bulk(d, size, rng):
+    x, y, z = W.jittered_cube(size, 1.0, rng)
+    return W.concat(d, W._pack(x, y, z + 50.0, np.full(x.size, 2.9), np.zeros(x.size), np.zeros(x.size)))
+
+
+def test_short_film_rows_beside_long_bulk_rows():
+    """Each model's kernel follows its own longest row: the position adjoint against the oracle (to 1e-9, as above), and its
+    film launch on 500^2 rows beside a bulk within 1.2 times the same launch without one (1.33 by the bulk's row length)."""
+    from paper_2405_13165_amd import gfdm as g
+    ctx = g.Context(0)
+    rng = np.random.default_rng(12)
+    d = with_bulk(film_cloud(30, rng), 12, rng)
+    p = g.Particles.from_dict(ctx, d)
+    nb = g.build_neighbours(ctx, p)
+    rp, col = (t.cpu().numpy() for t in nb.export())
+    assert 64 < nb.max_row <= 128 and np.diff(rp)[d["model"] == 1].max() <= 64
+    u, yb = rng.standard_normal(p.n), rng.standard_normal((4, p.n))
+    xb_o = oracle.weights_adjoint_x(d, rp, col, u, yb)
+    xb = g.gfdm_weights_adjoint(ctx, p, nb, torch.as_tensor(u, device=ctx.device), torch.as_tensor(yb, device=ctx.device))
+    assert np.abs(xb.cpu().numpy() - xb_o).max() <= 1e-9 * np.abs(xb_o).max()
+    best = []
+    film = film_cloud(500, rng)
+    for d in (film, with_bulk(film, 20, rng)):
+        p = g.Particles.from_dict(ctx, d)
+        nb = g.build_neighbours(ctx, p)
+        u = torch.as_tensor(rng.standard_normal(p.n), device=ctx.device)
+        yb = torch.as_tensor(rng.standard_normal((4, p.n)), device=ctx.device)
+        times = []
+        for k in range(12):
+            ctx.profile(True)
+            g.gfdm_weights_adjoint(ctx, p, nb, u, yb)
+            times.append(ctx.profile_read()["weights_adjoint_film"][1])
+            ctx.profile(False)
+        best.append(min(times[2:]))
+    assert best[1] < 1.2 * best[0]
