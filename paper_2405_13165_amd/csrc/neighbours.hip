@@ -1151,6 +1151,8 @@ struct TileGroups {
   int64_t tile_start[3];
   int64_t row_start[2];
   int64_t nrows[2];
+  int64_t uniq[2];       // first place of the range's tiles in the list of distinct indices,
+  int entries[2];        // and places per tile: what its rows can hold
 };
 constexpr int kTileEntries = kTileRows * kTileBandRow;  // entries one tile can hold
 constexpr int kTileThreads = 512;
@@ -1161,13 +1163,17 @@ __device__ inline int tile_group(const TileGroups &tg, int64_t t) {
   while (q + 1 < tg.nq && t >= tg.tile_start[q + 1]) ++q;
   return q;
 }
+// first place of tile t of range q
+__device__ inline int64_t tile_uniq(const TileGroups &tg, int q, int64_t t) {
+  return tg.uniq[q] + (t - tg.tile_start[q]) * tg.entries[q];
+}
 
 // One block per tile.  The tile's distinct indices go into an LDS hash set
 // (open addressing, linear probing); the lane that inserts a key also takes a
 // place for it in ulist (one counter update per wave).  The list is sorted in
 // groups of 64 in registers, a key's rank is its place in its group plus the
 // number of smaller keys of every other group (binary searches side by side),
-// the sorted list is written to uniq[kTileEntries t ...], and each entry's slot is
+// the sorted list is written to uniq[tile_uniq ...], and each entry's slot is
 // the rank kept beside its key, read at the table position its insertion found;
 // cnt[t] = number of distinct indices.  Each wave takes whole rows (w, w + 8,
 // ...), a lane at most two entries of each (rows hold at most kTileBandRow = 128
@@ -1283,7 +1289,7 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_unique(TileGroups tg, con
         if (o + k < NG && o + k != gi) rank += lo[k] + (l[k][lo[k]] < v ? 1 : 0);
     }
     if (v != kNoEntry) {
-      uniq[kTileEntries * t + rank] = v;
+      uniq[tile_uniq(tg, q, t) + rank] = v;
       int h = hash_slot(v);
       while (hkey[h] != v) h = (h + 1) & (kHashSize - 1);
       hrank[h] = (uint16_t)rank;
@@ -1300,15 +1306,15 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_unique(TileGroups tg, con
     if (jj[c] >= 0) slot[base[c >> 1] + lane + 64 * (c & 1)] = hrank[hh[c]];
 }
 
-// uniq (kTileEntries places per tile) -> tile_u (at the list offsets), a wave per tile
-__global__ void __launch_bounds__(kBlock) k_tile_compact(const int64_t *__restrict__ u_off,
+// uniq (at tile_uniq) -> tile_u (at the list offsets), a wave per tile
+__global__ void __launch_bounds__(kBlock) k_tile_compact(TileGroups tg, const int64_t *__restrict__ u_off,
                                                          const int32_t *__restrict__ uniq, int64_t nt,
                                                          int32_t *__restrict__ tile_u) {
   const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   if (t >= nt) return;
-  const int64_t b = u_off[t], m = u_off[t + 1] - b;
+  const int64_t a = tile_uniq(tg, tile_group(tg, t), t), b = u_off[t], m = u_off[t + 1] - b;
 #pragma unroll 4
-  for (int64_t s = threadIdx.x & 63; s < m; s += 64) tile_u[b + s] = uniq[kTileEntries * t + s];
+  for (int64_t s = threadIdx.x & 63; s < m; s += 64) tile_u[b + s] = uniq[a + s];
 }
 
 // reverse-edge map: rev[k] = position of (j, i) in row j for entry k = (i, j)
@@ -1677,7 +1683,7 @@ namespace {
 gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   hipStream_t sm = ctx->stream;
   TileGroups tg;
-  int64_t nt = 0;
+  int64_t nt = 0, places = 0;
   for (int m = 0; m < 2; ++m) {
     nb->tile_start[m] = nt;
     const int64_t r0 = nb->group_start[m * GF_NBAND], r1 = nb->group_start[m * GF_NBAND + kTileBand + 1];
@@ -1686,8 +1692,12 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
     tg.tile_start[tg.nq] = nt;
     tg.row_start[tg.nq] = r0;
     tg.nrows[tg.nq] = r1 - r0;
+    tg.uniq[tg.nq] = places;
+    tg.entries[tg.nq] = kTileRows * std::min(nb->model_row[m], kTileBandRow);
+    const int64_t k = (r1 - r0 + kTileRows - 1) / kTileRows;
+    places += k * tg.entries[tg.nq];
     ++tg.nq;
-    nt += (r1 - r0 + kTileRows - 1) / kTileRows;
+    nt += k;
   }
   nb->tile_start[2] = nt;
   tg.tile_start[tg.nq] = nt;
@@ -1697,12 +1707,12 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   if (!take(nb, nb->slot, nb->nnz + kQuadPad) || !take(nb, nb->tile_off, nt + 1))
     return set_error(ctx, GF_ENOMEM, "neighbour tile allocation failed");
   Arena ar;
-  std::vector<size_t> sz = {sizeof(int64_t) * scan_tmp_elems(nt + 1), sizeof(int32_t) * kTileEntries * (size_t)nt,
+  std::vector<size_t> sz = {sizeof(int64_t) * scan_tmp_elems(nt + 1), sizeof(int32_t) * (size_t)places,
                             sizeof(int32_t) * nt, 64};
   gf_status st;
   if ((st = ensure_scratch(ctx, arena_bytes(sz), &ar))) return st;
   int64_t *tmp64 = ar.take<int64_t>(scan_tmp_elems(nt + 1));
-  int32_t *uniq = ar.take<int32_t>(kTileEntries * (size_t)nt);
+  int32_t *uniq = ar.take<int32_t>((size_t)places);
   int32_t *cnt = ar.take<int32_t>(nt);
   int32_t *grp_max = ar.take<int32_t>(16);
   {
@@ -1723,8 +1733,8 @@ gf_status build_tiles(gf_ctx *ctx, gf_nbr *nb) {
   if (!take(nb, nb->tile_u, total))
     return set_error(ctx, GF_ENOMEM, "neighbour tile list allocation failed");
   ProfScope prof(ctx, "nbr_tile_compact");
-  hipLaunchKernelGGL(k_tile_compact, dim3(grid_for(nt, kBlock / 64)), dim3(kBlock), 0, sm, nb->tile_off, uniq, nt,
-                     nb->tile_u);
+  hipLaunchKernelGGL(k_tile_compact, dim3(grid_for(nt, kBlock / 64)), dim3(kBlock), 0, sm, tg, nb->tile_off, uniq,
+                     nt, nb->tile_u);
   GF_LAUNCH_CHECK(ctx);
   return GF_OK;
 }

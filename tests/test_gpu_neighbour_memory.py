@@ -150,3 +150,22 @@ def test_kept_memory_follows_the_clouds():
     nb = g.build_neighbours(ctx, pb)
     assert before - torch.cuda.mem_get_info(ctx.device)[0] < nb.nnz
     nb.close()
+
+
+def test_memory_of_a_film():
+    """A build of 8.1 million film rows of 28 entries (beyond the sizes whose rows are staged): the handle and the scratch
+    take less than 6 bytes per entry and 250 per particle."""
+    from paper_2405_13165_amd import gfdm as g
+    k = torch.arange(2850 * 2850, device="cuda")
+    x, y = (k % 2850).double(), (k // 2850).double()
+    gen = torch.Generator("cuda").manual_seed(4)
+    x, y = (a + 0.4 * torch.rand(len(k), generator=gen, device="cuda", dtype=torch.float64) for a in (x, y))
+    ctx = g.Context(0)
+    z = torch.zeros_like(x)
+    p = g.Particles(ctx, x, y, z, z + 3.0, torch.ones_like(k), torch.full_like(k, W.WALL), z, z, z + 1.0)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info(ctx.device)[0]
+    nb = g.build_neighbours(ctx, p)
+    assert 27 * p.n < nb.nnz < 30 * p.n
+    assert before - torch.cuda.mem_get_info(ctx.device)[0] < 6 * nb.nnz + 250 * p.n
+    nb.close()
