@@ -804,9 +804,6 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
         // (a particle lies in its cell's cube up to the rounding of its cell coordinate, below 1e-9 edges; the cubes are
         // taken from the grid's corner as that coordinate is, so this holds however far the corner is from the origin)
         const double edge = g.edge[ts], Rc = R + 1e-9 * edge;
-        double bl[3];  // the box's centre from the grid's corner
-#pragma unroll
-        for (int d = 0; d < 3; ++d) bl[d] = uniform_f64(bc[d] - g.lo[ts][d]);
 #pragma unroll 1
         for (unsigned kb = 0; kb < nbox; kb += 64) {
           int len = 0, rb = 0;
@@ -819,7 +816,7 @@ __global__ void __launch_bounds__(kSearchBlock) k_search(const int32_t *__restri
             double u2 = 0.0;
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-              const double lo = fma((double)cc[d], edge, -bl[d]);  // the cube's lower face, from the box's centre
+              const double lo = fma((double)cc[d], edge, g.lo[ts][d] - bc[d]);  // the cube's lower face, from the box's centre
               const double below = lo - be[d], above = cc[d] == g.dim[ts][d] - 1 ? 0.0 : -(lo + edge) - be[d];
               const double u = fmax(fmax(below, above), 0.0);
               u2 = fma(u, u, u2);
@@ -1310,7 +1307,7 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_unique(TileGroups tg, con
 __global__ void __launch_bounds__(kBlock) k_tile_compact(TileGroups tg, const int64_t *__restrict__ u_off,
                                                          const int32_t *__restrict__ uniq, int64_t nt,
                                                          int32_t *__restrict__ tile_u) {
-  const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (t >= nt) return;
   const int64_t a = tile_uniq(tg, tile_group(tg, t), t), b = u_off[t], m = u_off[t + 1] - b;
 #pragma unroll 4
@@ -1924,7 +1921,7 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
     hipLaunchKernelGGL(k_cell_sort_big, dim3((unsigned)std::min<int64_t>(n / kUnitSmall + 1, 4 * ctx->num_cu)),
                        dim3(kBlock), 0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, gg, ord, recs, skey, slot);
     if (n > kCellSort)  // (slot[] is free after the scatter)
-      hipLaunchKernelGGL(k_cell_merge, dim3((unsigned)std::min<int64_t>(n / kCellSort + 1, 4 * ctx->num_cu)), dim3(kBlock),
+      hipLaunchKernelGGL(k_cell_merge, dim3((unsigned)std::min<int64_t>(n / kCellSort + 1, ctx->num_cu)), dim3(kBlock),
                          0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, skey, slot, ord, recs);
     return hipGetLastError() == hipSuccess ? GF_OK : set_error(ctx, GF_EHIP, "cell order kernels failed");
   };
