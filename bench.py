@@ -532,11 +532,12 @@ def main():
         result["rows"] = rows
         result["rows_kernels_us"] = kern
         # algorithmic bytes of each row (per particle N and per neighbour entry nnz, each byte a row
-        # must read or write at least once)
+        # must read or write at least once; the adjoints on this cloud's tiles: an entry's stencil once,
+        # its 2-byte slot and its 2 bytes of the transposed tile)
         film_nnz = float((np.diff(rp)[d["model"] == 1]).sum())
         row_bytes = {"build_neighbours": 4.0 * nnz + 41.0 * N, "classify_pca": 4.0 * nnz + 106.0 * N,
                      "apply": 18.0 * nnz + 40.0 * N, "transition": 4.0 * nnz + 48.0 * N,
-                     "apply_adjoint": 48.0 * nnz + 16.0 * N, "weights_adjoint": 80.0 * nnz + 56.0 * N,
+                     "apply_adjoint": 20.0 * nnz + 16.0 * N, "weights_adjoint": 4.0 * nnz + 96.0 * N,
                      "film_height": 4.0 * film_nnz + 60.0 * float((d["model"] == 1).sum()) + 13.0 * N,
                      "buffer_zone": 60.0 * N}
         roof_rows = {}

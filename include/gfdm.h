@@ -305,7 +305,13 @@ typedef struct {
                          declared (no restart of the Krylov space).
                          2: iterative refinement with restarts: r = b - A x in
                          FP64, an inner Jacobi-BiCGStab on FP32 values and FP32
-                         vectors solves A d = r, x += d. */
+                         vectors solves A d = r, x += d.  The least memory traffic
+                         per iteration, but each restart loses the Krylov space, and
+                         on large systems rounding decides the number of iterations
+                         (832 to 1,880 on a 4.0M-row cylinder, 476 to 580 with 0).
+                         Take 1 unless FP32 vectors are what is wanted: it was never
+                         slower (401,320 rows: 30 ms, 31 with 2, 38 with 0; 4.0M:
+                         0.86 s, 1.5 to 2.6, 1.0). */
   double inner_rtol;  /* mixed = 2: relative reduction per inner solve, 1e-4 (an
                          inner solve never aims below half the overall target) */
   int inner_maxit;    /* mixed = 2: inner iteration limit per refinement, 2000 */
@@ -476,7 +482,8 @@ gf_status gf_transition_3d_to_2d_cloud(gf_ctx *ctx, const gf_particles *p, const
 /* ---------------------------------------------------------- adjoints */
 /* Transpose of gf_apply_stencil with respect to u: ubar = C^T ybar, where
  * ybar [K][n] FP64 holds dL/dout; ubar [n] FP64 is overwritten.
- * Deterministic (every sum has a fixed order, no atomics).  With
+ * Deterministic (every sum has a fixed order, no atomics; the order is that of
+ * the neighbour tiles, the same for every handle built of the same particles).  With
  * extended neighbourhoods (gf_build_neighbours_rows) the ghost particles,
  * whose rows hold only themselves, receive nothing from the rows that list
  * them; every other term is as for symmetric lists. */

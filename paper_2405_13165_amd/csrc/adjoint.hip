@@ -17,7 +17,8 @@
 // contributions go to scratch with the rows laid out in grouped (Morton) order
 // and are gathered per particle, in the same order, through the reverse-edge
 // map: the twin entry (j, i) of (i, j) lies in a Morton-near row, so the gather
-// stays in L2.  No atomics: the result is deterministic.
+// stays in L2.  No atomics: the result is deterministic, and as the tiles follow
+// the cell order, which is fixed, the same for every handle of a cloud.
 // Rows whose forward stencils are zero (status 2 or 3 of the stencil call,
 // when the caller passes those statuses) contribute nothing, and so do rows
 // whose Gram matrix is not positive definite.

@@ -110,12 +110,12 @@ struct WRec<double> {
 // survive in L2 between the two when every CU keeps hundreds of rows in flight.
 //
 // What bounds it: HBM (18 bytes per entry with FP32 stencils).  Mixed cloud
-// (534 MB of stencils, four operators) 160 -> 141 us, at an eighth of that size
-// 23.6 -> 19.1 us; with four or seven records ahead 154 and 180 us, without the
-// aligned start 168 us.  NT (stencils beyond the Infinity Cache, FP32): 141
-// against 150 us, but 55 against 43 us at 200 MB, which stay cached between
-// calls; FP64 records, whose lines two instructions share, lose by it (270
-// against 250 us).
+// (534 MB of stencils, four operators) 158 -> 147.6 us over repeated calls; in one
+// trial after another (141 us then) with four or seven records ahead 154 and 180 us,
+// without the aligned start 168 us, without NT (stencils beyond the Infinity Cache,
+// FP32) 150 us; at an eighth of the size 23.6 -> 19.1 us.  NT takes 55 against 43 us
+// at 200 MB, which stay cached between calls; FP64 records, whose lines two
+// instructions share, lose by it (270 against 250 us).
 struct ApplyTiles {
   const int32_t *grouped;
   int nranges;

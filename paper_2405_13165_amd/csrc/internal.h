@@ -156,8 +156,8 @@ constexpr int kTileRows = 32;
 constexpr int kSlotNone = 0xffff;
 constexpr int kTileBand = 2;                   // bands 0..kTileBand are tiled
 constexpr int kTileBandRow = 128;              // = kBandHi[kTileBand]
-// entries of padding after the slot array (and the solver's matrix values),
-// so that the SpMV can read a row's entries in aligned groups of four
+// entries of padding after the slot array: the tiled PCA reads a row's slots in
+// aligned groups of four, of which the last may reach past the last row
 constexpr int kQuadPad = 4;
 
 // where the tiles' rows lie in the grouped order
