@@ -318,9 +318,10 @@ __global__ void __launch_bounds__(kBlock) k_keys(const double *__restrict__ x, c
 // grid, cells - 1): such a block, or each of its cells where it holds more than
 // kCellSort particles; those of more than kUnitSmall rows in a list of their own as
 // (first row, rows, grid, piece), a cell of more than kCellSort once for each piece
-// of kCellSort rows.  And the number of particles of each grid.
+// of kUnitSmall rows.  And the number of particles of each grid.
 constexpr int kUnitSmall = 256;
 constexpr int kCellSort = 2048;
+inline int64_t big_units(int64_t n) { return n / kUnitSmall + n / kCellSort + 1; }  // at most
 constexpr int kItemFill = 20;
 constexpr int kItemBits = 3;
 struct CellLists {
@@ -379,7 +380,7 @@ __global__ void __launch_bounds__(kItemsBlock) k_items(const int32_t *__restrict
     for (int c = 0; c < cells; ++c) {
       const int ca = cell_start[k + c], cl = cell_start[k + c + 1] - ca;
       if (cl > kUnitSmall) {
-        const int np = (cl + kCellSort - 1) / kCellSort, at = atomicAdd(out.nbig, np);
+        const int np = cl > kCellSort ? (cl + kUnitSmall - 1) / kUnitSmall : 1, at = atomicAdd(out.nbig, np);
         for (int q = 0; q < np; ++q) out.big[at + q] = make_int4(ca, cl, s, q);
       } else if (cl > 0) {
         out.units[atomicAdd(out.nunits, 1)] = make_int4(ca, cl, s, 0);
@@ -434,7 +435,8 @@ constexpr int kCellSortWaves = 4;
 __global__ void __launch_bounds__(64 * kCellSortWaves) k_cell_sort_small(
     const int4 *__restrict__ units, const int32_t *__restrict__ nunits, const int32_t *__restrict__ key,
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
-    const double *__restrict__ h, Grid g, int32_t *order, double4 *__restrict__ sp) {
+    const double *__restrict__ h, Grid g, const int32_t *__restrict__ raw, int32_t *__restrict__ order,
+    double4 *__restrict__ sp) {
   constexpr int NV = kUnitSmall / 64;
   __shared__ __attribute__((aligned(16))) uint64_t s_key[kCellSortWaves][kUnitSmall];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -451,7 +453,7 @@ __global__ void __launch_bounds__(64 * kCellSortWaves) k_cell_sort_small(
       id[q] = 0;
       uint64_t k = ~0ull;
       if (t < len) {
-        const int32_t i = order[b + t];
+        const int32_t i = raw[b + t];
         id[q] = i;
         rec[q] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
         const uint32_t cell = (uint32_t)(key[i] - (int32_t)g.base[s]) & (uint32_t)un.w;
@@ -481,9 +483,12 @@ __global__ void __launch_bounds__(64 * kCellSortWaves) k_cell_sort_small(
 }
 
 // Larger units, a block each, by a bitonic network in LDS over the whole fine
-// key.  The pieces of a cell of more than kCellSort particles leave their keys and
-// indices to k_cell_merge.  The neighbour sets do not depend on this order, but the
-// tiles and so the order of the adjoints' sums do: it is the same for every build.
+// key.  A cell of more than kCellSort particles takes a block per kUnitSmall of
+// them, each of which counts how many of the cell's come before its own (2^12
+// sub-keys, packed with the index as above): cells so full cost their pairs in the
+// search too (8,000 particles in one cell: 115 us here, 360 there), and a launch
+// that would merge sorted pieces takes 4 us in every build.  The neighbour sets do not depend on this order, but the tiles and so
+// the order of the adjoints' sums do: it is the same for every build.
 __device__ inline uint64_t fine_key(double x, double y, double z, const Grid &g, int s) {
   const double f = (double)(1 << kSubBits);
   int c[3];
@@ -500,22 +505,46 @@ __device__ inline uint64_t fine_key(double x, double y, double z, const Grid &g,
   return key;
 }
 
+static_assert(kBlock == kUnitSmall, "a thread per particle of a piece");
 __global__ void __launch_bounds__(kBlock) k_cell_sort_big(const int4 *__restrict__ units, const int32_t *__restrict__ nunits,
                                                           const double *__restrict__ x, const double *__restrict__ y,
                                                           const double *__restrict__ z, const double *__restrict__ h,
-                                                          Grid g, int32_t *order, double4 *__restrict__ sp,
-                                                          uint64_t *__restrict__ skey, int32_t *__restrict__ sid) {
-  __shared__ uint64_t kk[kCellSort];
+                                                          Grid g, const int32_t *__restrict__ raw,
+                                                          int32_t *__restrict__ order, double4 *__restrict__ sp) {
+  __shared__ __attribute__((aligned(16))) uint64_t kk[kCellSort];
   __shared__ int32_t id[kCellSort];
   const int nu = *nunits;
   for (int u = blockIdx.x; u < nu; u += gridDim.x) {
     const int4 un = units[u];
-    const int b = un.x + un.w * kCellSort, len = min(kCellSort, un.y - un.w * kCellSort), s = un.z;
+    const int b = un.x, len = un.y, s = un.z;
+    if (len > kCellSort) {
+      const int t = un.w * kUnitSmall + (int)threadIdx.x;  // this thread's particle of the cell
+      auto packed = [&](int32_t i) { return ((uint64_t)fine_sub(x[i], y[i], z[i], g, s) << 32) | (uint32_t)i; };
+      const int32_t mine = t < len ? raw[b + t] : 0;
+      const uint64_t key = packed(mine);
+      int rank = 0;
+      for (int c = 0; c < len; c += kCellSort) {
+        const int m = min(kCellSort, len - c);
+        for (int q = threadIdx.x; q < kCellSort; q += kBlock) kk[q] = q < m ? packed(raw[b + c + q]) : ~0ull;
+        __syncthreads();
+#pragma unroll 4
+        for (int q = 0; q < m; q += 2) {  // (an odd count's last pair ends in a pad, which is not smaller)
+          const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(&kk[q]);
+          rank += (v.x < key) + (v.y < key);
+        }
+        __syncthreads();
+      }
+      if (t < len) {
+        order[b + rank] = mine;
+        if (sp) sp[b + rank] = make_double4(x[mine], y[mine], z[mine], 0.5 * h[mine]);
+      }
+      continue;
+    }
     int P = 1;
     while (P < len) P <<= 1;
     for (int t = threadIdx.x; t < P; t += kBlock) {
       if (t < len) {
-        const int32_t i = order[b + t];
+        const int32_t i = raw[b + t];
         kk[t] = fine_key(x[i], y[i], z[i], g, s);
         id[t] = i;
       } else {
@@ -541,50 +570,10 @@ __global__ void __launch_bounds__(kBlock) k_cell_sort_big(const int4 *__restrict
     }
     for (int t = threadIdx.x; t < len; t += kBlock) {
       const int32_t i = id[t];
-      if (un.y > kCellSort) {
-        skey[b + t] = kk[t];
-        sid[b + t] = i;
-        continue;
-      }
       order[b + t] = i;
       if (sp) sp[b + t] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
     }
     __syncthreads();
-  }
-}
-
-// The sorted pieces of a cell merged, a block per piece: a particle goes behind
-// the smaller ones of every piece, found by binary search.  A million particles in
-// one cell take 488 searches each; the search tests all their pairs.
-__global__ void __launch_bounds__(kBlock) k_cell_merge(const int4 *__restrict__ units, const int32_t *__restrict__ nunits,
-                                                       const double *__restrict__ x, const double *__restrict__ y,
-                                                       const double *__restrict__ z, const double *__restrict__ h,
-                                                       const uint64_t *__restrict__ skey, const int32_t *__restrict__ sid,
-                                                       int32_t *__restrict__ order, double4 *__restrict__ sp) {
-  const int nu = *nunits;
-  for (int u = blockIdx.x; u < nu; u += gridDim.x) {
-    const int4 un = units[u];
-    if (un.y <= kCellSort) continue;
-    const int b = un.x + un.w * kCellSort, len = min(kCellSort, un.y - un.w * kCellSort);
-    for (int t = threadIdx.x; t < len; t += kBlock) {
-      const uint64_t key = skey[b + t];
-      const int32_t i = sid[b + t];
-      int at = un.x + t;
-      for (int o = 0; o * kCellSort < un.y; ++o) {
-        if (o == un.w) continue;
-        const int ob = un.x + o * kCellSort;
-        int lo = 0, hi = min(kCellSort, un.y - o * kCellSort);
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          const uint64_t v = skey[ob + mid];
-          if (v < key || (v == key && sid[ob + mid] < i)) lo = mid + 1;
-          else hi = mid;
-        }
-        at += lo;
-      }
-      order[at] = i;
-      if (sp) sp[at] = make_double4(x[i], y[i], z[i], 0.5 * h[i]);
-    }
   }
 }
 
@@ -1860,8 +1849,8 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   sz = {sizeof(int32_t) * n, sizeof(int32_t) * n, sizeof(int32_t) * (K + 1), sizeof(int32_t) * scan_tmp_elems(K + 1),
         sizeof(double4) * (n + kRowPad), sizeof(int32_t) * n, sizeof(int64_t) * scan_tmp_elems(n + 1),
         sizeof(int32_t) * 32, sizeof(int32_t) * n, sizeof(int32_t) * (n + 1), sizeof(int32_t) * scan_tmp_elems(n + 1),
-        sizeof(int32_t) * n, sizeof(int4) * n, sizeof(int4) * n, sizeof(int4) * (n / kUnitSmall + 1),
-        sizeof(int32_t) * (n + kRowPad), sizeof(uint64_t) * (n > kCellSort ? n : 0)};
+        sizeof(int32_t) * n, sizeof(int4) * n, sizeof(int4) * n, sizeof(int4) * big_units(n),
+        sizeof(int32_t) * (n + kRowPad)};
   // rows staged by the count pass (sw entries each, the widest that stays
   // under 8 GB); rows found longer are filled by a second search pass
   int sw = 0;
@@ -1887,9 +1876,8 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
   int32_t *order1 = ar.take<int32_t>(n);  // model-wide cell order for the grouping (several levels)
   int4 *items = ar.take<int4>(n);
   int4 *units = ar.take<int4>(n);
-  int4 *big = ar.take<int4>(n / kUnitSmall + 1);
+  int4 *big = ar.take<int4>(big_units(n));
   int32_t *order = ar.take<int32_t>(n + kRowPad);  // particles in cell order
-  uint64_t *skey = ar.take<uint64_t>(n > kCellSort ? n : 0);  // keys of the pieces of very full cells
   int32_t *stage = use_stage ? ar.take<int32_t>((size_t)n * sw) : nullptr;
 
   gf_nbr *nb = new gf_nbr();
@@ -1914,15 +1902,13 @@ extern "C" gf_status gf_build_neighbours_rows(gf_ctx *ctx, const gf_particles *p
     if (s2) return s2;
     hipLaunchKernelGGL(k_items, dim3(grid_for(KK, kItemsBlock)), dim3(kItemsBlock), 0, sm, cell_start, gg, kItemRows,
                        lists);
-    hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, ord);
+    int32_t *raw = gflag;  // (free until the grouping) the cells' particles in the order of their atomics
+    hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, sm, key, slot, cell_start, n, raw);
     hipLaunchKernelGGL(k_cell_sort_small, dim3((unsigned)std::min<int64_t>(n / (8 * kCellSortWaves) + 1, 8 * ctx->num_cu)),
-                       dim3(64 * kCellSortWaves), 0, sm, lists.units, lists.nunits, key, p->x, p->y, p->z, p->h, gg, ord,
-                       recs);
+                       dim3(64 * kCellSortWaves), 0, sm, lists.units, lists.nunits, key, p->x, p->y, p->z, p->h, gg, raw,
+                       ord, recs);
     hipLaunchKernelGGL(k_cell_sort_big, dim3((unsigned)std::min<int64_t>(n / kUnitSmall + 1, 4 * ctx->num_cu)),
-                       dim3(kBlock), 0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, gg, ord, recs, skey, slot);
-    if (n > kCellSort)  // (slot[] is free after the scatter)
-      hipLaunchKernelGGL(k_cell_merge, dim3((unsigned)std::min<int64_t>(n / kCellSort + 1, ctx->num_cu)), dim3(kBlock),
-                         0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, skey, slot, ord, recs);
+                       dim3(kBlock), 0, sm, lists.big, lists.nbig, p->x, p->y, p->z, p->h, gg, raw, ord, recs);
     return hipGetLastError() == hipSuccess ? GF_OK : set_error(ctx, GF_EHIP, "cell order kernels failed");
   };
   {
